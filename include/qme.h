@@ -576,6 +576,16 @@ qme_status qme_set_fold(qme_ctx *ctx, int32_t enable);
  * split off).  Other values: QME_E_ARG. */
 qme_status qme_set_direct_loads(qme_ctx *ctx, int32_t mode);
 
+/* How the steps (and the adjoint's) apply the propagator U = exp(-i H dt):
+ * 0 as a dense matrix in two matrix products, 1 by its Taylor series in two
+ * passes over the rows of the state (H is sparse: a few multiply-adds per
+ * element and term in place of N), -1 (default) by the series where it is the
+ * faster form (a rule on N, H's couplings and |H dt|) and qme_set_split has
+ * not asked for split products.  Tiles, splits and direct loads are knobs of
+ * the dense products.  The forms agree to rounding.  1 for a context without
+ * a series form: QME_E_UNSUPPORTED; other values: QME_E_ARG. */
+qme_status qme_set_products(qme_ctx *ctx, int32_t form);
+
 /* Graph replay of qme_step (off by default): with enable = 1, a call of
  * n_steps on a given (state, workspace) pair is captured once into a
  * hipGraph on a private stream and replayed onto the caller's stream with

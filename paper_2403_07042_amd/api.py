@@ -348,6 +348,12 @@ class Solver:
         blocks per compute unit.  Bitwise-neutral."""
         L.check(self.lib.qme_set_direct_loads(self.ctx, int(mode)))
 
+    def set_products(self, form: int):
+        """The propagator in the steps: 0 as a dense matrix (matrix-core
+        products), 1 by its Taylor series, -1 (default) by the series where
+        it is faster."""
+        L.check(self.lib.qme_set_products(self.ctx, int(form)))
+
     def set_graph(self, enable: bool):
         """Replay qme_step runs from captured hipGraphs (off by default)."""
         L.check(self.lib.qme_set_graph(self.ctx, int(bool(enable))))

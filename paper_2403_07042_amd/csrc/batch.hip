@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <climits>
 #include <cmath>
 #include <map>
@@ -28,6 +29,7 @@
 #include "device.hpp"
 #include "dissipate_tile.hpp"
 #include "qme.h"
+#include "series_tile.hpp"
 
 namespace qme {
 
@@ -45,6 +47,9 @@ struct BatchInstance {
   int32_t n_gather;
   uint32_t items[4];   // per phase: tiles1^2, lower tiles2, 1, lower tiles (decoherence)
   DissArgs<float> sparse;   // the sparse-channel fields only (see DissArgs)
+  // row passes of instances whose steps apply the propagator's series (in
+  // place of phases 0 and 1)
+  SeriesArgs<float> first, second;
 };
 
 struct BatchPhase {
@@ -158,6 +163,20 @@ __global__ __launch_bounds__(kBatchThreads) void batch_phase_kernel(BatchPhase p
   const int lo = find_position(p.off, p.count, r);
   batch_item<PHASE, SPARSE>(p.inst[p.order[lo]], int(r - p.off[lo]), smem, p.slot_in, p.slot_out,
                             p.fuse != 0);
+}
+
+// Phases 0 and 1 of the instances that take the series: one workgroup per
+// group of R rows, of all of them (a batch's passes share one shape, that of
+// the largest).
+template <int R, int S, int NT, int MODE>
+__global__ __launch_bounds__(NT, 4) void batch_series_kernel(BatchPhase p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int64_t r = blockIdx.x;
+  const int lo = find_position(p.off, p.count, r);
+  const int i = __builtin_amdgcn_readfirstlane(p.order[lo]);
+  const int group = __builtin_amdgcn_readfirstlane(int(r - p.off[lo]));
+  series_rows<float, R, S, NT, MODE>(MODE == kSeriesFirst ? p.inst[i].first : p.inst[i].second,
+                                     group, lds);
 }
 
 // After a run of fused steps that ended in slot pair 1, every instance's
@@ -323,8 +342,12 @@ struct qme_batch {
   // device tables (owned)
   BatchInstance *inst = nullptr;
   int32_t *order = nullptr;
-  int64_t *phase_off = nullptr;   // [4][count + 1]
-  int64_t phase_items[4] = {0, 0, 0, 0};
+  // item offsets: the four phases (0 and 1: instances with dense products),
+  // then the row groups of the instances that take the series, those in
+  // 16-byte units and those in 8-byte ones
+  int64_t *phase_off = nullptr;   // [6][count + 1]
+  int64_t phase_items[6] = {0, 0, 0, 0, 0, 0};
+  int64_t series_n[2] = {0, 0};   // the largest N of each
   size_t ws_bytes = 0;
   std::vector<size_t> ws_off;      // per instance: Y planes offset (Z follows)
   hipStream_t capture_stream = nullptr;
@@ -388,6 +411,8 @@ static qme_status build_tables(qme_batch *b) {
     std::stable_sort(ord.begin(), ord.end(),
                      [&](int x, int y) { return b->ctxs[x]->n > b->ctxs[y]->n; });
   std::vector<BatchInstance> tab(nb);
+  std::vector<std::array<int64_t, 2>> groups(nb);
+  b->series_n[0] = b->series_n[1] = 0;
   b->ws_off.assign(nb, 0);
   size_t off = 0;
   for (int i = 0; i < nb; ++i) {
@@ -419,6 +444,14 @@ static qme_status build_tables(qme_batch *b) {
     c->sparse_args(t.sparse);
     if (t.sparse.n_csr > 0 || t.sparse.koff_ptr) b->sparse = true;
     const int td = int((c->n + TD - 1) / TD);
+    groups[i] = {0, 0};
+    if (uses_series(c)) {
+      const int cls = series_slot_bytes(c->n) == 16 ? 0 : 1, rows = cls == 0 ? 4 : 2;
+      groups[i][cls] = (c->n + rows - 1) / rows;
+      b->series_n[cls] = std::max(b->series_n[cls], c->n);
+      t.first = series_args<float>(c, t.x_re, t.x_im, nullptr, nullptr, 1, false);
+      t.second = series_args<float>(c, nullptr, nullptr, nullptr, nullptr, 1, false);
+    }
     t.items[0] = uint32_t(t.tiles1) * uint32_t(t.tiles1);
     t.items[1] = uint32_t(t.tiles2) * uint32_t(t.tiles2 + 1) / 2;
     t.items[2] = 1;
@@ -429,12 +462,14 @@ static qme_status build_tables(qme_batch *b) {
   b->ctr_off = off;
   off += a256(sizeof(uint32_t) * size_t(nb)) + 256;
   b->ws_bytes = off;
-  std::vector<int64_t> po(4 * (nb + 1), 0);
-  for (int ph = 0; ph < 4; ++ph) {
+  std::vector<int64_t> po(6 * (nb + 1), 0);
+  for (int ph = 0; ph < 6; ++ph) {
     int64_t acc = 0;
     for (int k = 0; k < nb; ++k) {
       po[ph * (nb + 1) + k] = acc;
-      acc += tab[ord[k]].items[ph];
+      const std::array<int64_t, 2> &g = groups[ord[k]];
+      if (ph >= 4) acc += g[ph - 4];
+      else if (ph >= 2 || g[0] + g[1] == 0) acc += tab[ord[k]].items[ph];
     }
     po[ph * (nb + 1) + nb] = acc;
     b->phase_items[ph] = acc;
@@ -461,6 +496,12 @@ static qme_status bind_workspace(qme_batch *b, char *ws) {
     tab[i].y_im = y + pe;
     tab[i].z_re = y + 2 * pe;
     tab[i].z_im = y + 3 * pe;
+    tab[i].first.o_re = y;
+    tab[i].first.o_im = y + pe;
+    tab[i].second.x_re = y;
+    tab[i].second.x_im = y + pe;
+    tab[i].second.o_re = y + 2 * pe;
+    tab[i].second.o_im = y + 3 * pe;
   }
   B_OK(hipMemcpy(b->inst, tab.data(), sizeof(BatchInstance) * b->count, hipMemcpyHostToDevice));
   b->last_ws = ws;
@@ -502,11 +543,47 @@ static hipError_t enqueue_persistent(qme_batch *b, int64_t n_steps, hipStream_t 
   return hipGetLastError();
 }
 
+template <int R, int S, int NT>
+static hipError_t enqueue_series(const BatchPhase &p, int mode, int64_t items, hipStream_t s) {
+  constexpr size_t lds = size_t(2) * S * NT * R * sizeof(float);
+  const auto kernel = mode == kSeriesFirst ? batch_series_kernel<R, S, NT, kSeriesFirst>
+                                           : batch_series_kernel<R, S, NT, kSeriesLower>;
+  if (lds > 48 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(unsigned(items)), dim3(NT), lds, s, p);
+  return hipGetLastError();
+}
+
+// Phase `mode` (0 or 1) of the instances that take the series.
+static hipError_t enqueue_series_phase(qme_batch *b, int mode, hipStream_t s) {
+  for (int cls = 0; cls < 2; ++cls) {
+    const int64_t items = b->phase_items[4 + cls], n = b->series_n[cls];
+    if (items == 0) continue;
+    const BatchPhase p{b->inst, b->order, b->phase_off + (4 + cls) * (b->count + 1), b->count};
+    const hipError_t e = cls == 1    ? enqueue_series<2, 8, 1024>(p, mode, items, s)
+                         : n <= 256  ? enqueue_series<4, 1, 256>(p, mode, items, s)
+                         : n <= 512  ? enqueue_series<4, 2, 256>(p, mode, items, s)
+                         : n <= 1024 ? enqueue_series<4, 2, 512>(p, mode, items, s)
+                         : n <= 4096 ? enqueue_series<4, 4, 1024>(p, mode, items, s)
+                                     : enqueue_series<4, 5, 1024>(p, mode, items, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 static hipError_t enqueue(qme_batch *b, int64_t n_steps, hipStream_t s) {
   if (b->persistent) return enqueue_persistent(b, n_steps, s);
   for (int64_t k = 0; k < n_steps; ++k) {
     const int parity = b->fuse ? int(k & 1) : 0;
     for (int ph = 0; ph < 4; ++ph) {
+      if (ph <= 1) {
+        const hipError_t e = enqueue_series_phase(b, ph == 0 ? kSeriesFirst : kSeriesLower, s);
+        if (e != hipSuccess) return e;
+        if (b->phase_items[ph] == 0) continue;   // no instance with dense products
+      }
       if (ph == 2 && b->fuse) continue;   // formed by the decoherence phase's blocks
       BatchPhase p{b->inst, b->order, b->phase_off + ph * (b->count + 1), b->count};
       if (b->fuse) {

@@ -253,7 +253,16 @@ hipError_t step_once(qme_ctx *c, const void *in, void *out, void *y, void *z, hi
   plan_product<T>(c, g2, c->tile2, true, area, o_re, 2 * pe);
   o1.wide = wide_first(c, g1);
   hipError_t e = mark(c, s, -1);
-  if constexpr (sizeof(T) == 4) {
+  if (uses_series(c)) {
+    // y = (rho conj(U))^dag, z = y conj(U) (lower triangle)
+    if (e == hipSuccess)
+      e = launch_series_pass<T>(series_args<T>(c, x_re, x_im, y_re, y_im, 1, false),
+                                kSeriesFirst, s);
+    if (e == hipSuccess) e = mark(c, s, 0);
+    if (e == hipSuccess)
+      e = launch_series_pass<T>(series_args<T>(c, static_cast<const T *>(y_re), y_im, z_re, z_im, 1, false),
+                                kSeriesLower, s);
+  } else if constexpr (sizeof(T) == 4) {
     if (c->precision == QME_BF16X3) {
       // dU pre-split (six bf16 planes, split once per context) for both
       // products: the first reads it as A, the lower-triangle one as M
@@ -289,6 +298,11 @@ template hipError_t step_once<double>(qme_ctx *, const void *, void *, void *, v
 // its blocks reads the N diagonal values of the rotated state once more).
 static constexpr int64_t kFuseTraceMaxN = 1024;
 
+bool uses_series(const qme_ctx *c) {
+  if (c->series_order == 0 || c->products == 0) return false;
+  return c->products == 1 || (c->series_faster && !c->split_asked);
+}
+
 bool fuse_trace_applies(const qme_ctx *c) {
   return c->n <= kFuseTraceMaxN && !uses_small_path(c) && !uses_fold(c);
 }
@@ -304,6 +318,7 @@ bool uses_small_path(const qme_ctx *c) {
 // element), in FP32 with 64-tiles for the lower product or in FP64.
 bool uses_fold(const qme_ctx *c) {
   if (!c->fold || c->jt.n_gather != 0 || c->jt.n_csr != 0) return false;
+  if (uses_series(c)) return true;
   if (c->precision == QME_FP32) return c->tile2 == 64 || c->tile2 == 32;
   return c->precision == QME_FP64 || c->precision == QME_BF16X3;
 }
@@ -317,6 +332,76 @@ static T *split_area_of(const qme_ctx *c, void *ws) {
   if (c->split_elems == 0) return nullptr;
   return reinterpret_cast<T *>(static_cast<char *>(ws) + align256(4 * plane_elems(c) * sizeof(T)) +
                                align256(sizeof(double) * size_t(c->n)));
+}
+
+// Whether a folded step's trace is formed by the next step's first product:
+// FP32 first products in 64- or 128-tiles or whole 32-tile panels and
+// BF16x3 ones in 128 x 64 tiles, without a split, form the previous step's
+// trace themselves (every block sums the stored diagonal,
+// block 0 stores the scalars), so the trace pass runs once per call, after
+// the last step; the sink and step count alternate between the scalar
+// pairs by step parity (as for the unfolded steps)
+template <typename T>
+static bool trace_in_first_product(const qme_ctx *c, T *area) {
+  if constexpr (sizeof(T) == 4) {
+    CgemmArgs<T> probe{};
+    probe.ld = c->ld;
+    if (c->precision == QME_FP32 && c->tile1 != 32) {
+      plan_product<T>(c, probe, c->tile1, false, area, nullptr, 0);
+      return probe.split <= 1;
+    }
+    // (and FP32 32-tile first products that load whole panels)
+    if (c->precision == QME_FP32) return c->ld <= kPanelLd && c->direct != 0;
+    // (and BF16x3 first products on 128 x 64 tiles)
+    plan_product<T>(c, probe, plan_tile1(c), false, area, nullptr, 0);
+    return wide_first(c, probe);
+  }
+  return false;
+}
+
+// Folded steps by the series: the second pass writes the decoherence step of
+// its rows (unscaled) into the state; the factor of step k is applied by the
+// second pass of step k + 1, so that the trace it comes from can be formed
+// beside the first one.  Under profiling the trace keeps the launches that
+// the dense step would give it (the same sums, bitwise), so that the launch
+// counts per kind mean the same for both forms.
+template <typename T>
+static hipError_t series_fold_steps(qme_ctx *c, void *state, int64_t n_steps, void *ws,
+                                    hipStream_t s) {
+  const size_t pe = plane_elems(c);
+  T *x_re = static_cast<T *>(state), *x_im = x_re + pe;
+  double *aux = reinterpret_cast<double *>(x_im + pe);
+  T *y_re = static_cast<T *>(ws), *y_im = y_re + pe;
+  double *zdiag = reinterpret_cast<double *>(static_cast<char *>(ws) +
+                                             align256(4 * pe * sizeof(T)));
+  const bool beside = !c->profiling || trace_in_first_product<T>(c, split_area_of<T>(c, ws));
+  const DissArgs<T> da{nullptr, nullptr, x_re, x_im, c->ld, c->n, c->model.dt, c->d, c->leak,
+                       c->pi, c->cg, 0, aux, aux, c->trw, zdiag};
+  for (int64_t k = 0; k < n_steps; ++k) {
+    SeriesArgs<T> first = series_args<T>(c, x_re, x_im, y_re, y_im, 1, false);
+    if (k > 0 && beside) {
+      first.tr_zdiag = zdiag;
+      first.tr_w = c->trw;
+      first.tr_leak = c->leak;
+      first.tr_aux = aux;
+      first.tr_dt = c->model.dt;
+    }
+    SeriesArgs<T> second = series_args<T>(c, y_re, y_im, x_re, x_im, 1, false);
+    if (k > 0) second.scale = aux + 4;
+    second.fold_d = c->d;
+    second.fold_dt = c->model.dt;
+    second.zdiag = zdiag;
+    hipError_t e = mark(c, s, -1);
+    if (e == hipSuccess) e = launch_series_pass<T>(first, kSeriesFirst, s);
+    if (e == hipSuccess) e = mark(c, s, 0);
+    if (e == hipSuccess) e = launch_series_pass<T>(second, kSeriesFold, s);
+    if (e == hipSuccess) e = mark(c, s, 1);
+    if (e == hipSuccess && (!beside || k == n_steps - 1)) e = launch_trace<T>(da, s);
+    if (e == hipSuccess) e = mark(c, s, 2);
+    if (e != hipSuccess) return e;
+  }
+  launch_timer() = nullptr;   // the closing pass is no step's kernel
+  return n_steps > 0 ? launch_series_close<T>(x_re, x_im, c->ld, c->n, aux + 4, s) : hipSuccess;
 }
 
 // Folded steps: the lower-triangle product writes the decoherence step of
@@ -336,29 +421,7 @@ static hipError_t fold_steps(qme_ctx *c, void *state, int64_t n_steps, void *ws,
   T *area = split_area_of<T>(c, ws);
   const T *u_re = static_cast<const T *>(c->du_re), *u_im = static_cast<const T *>(c->du_im);
   const double dt = c->model.dt;
-  // FP32 first products in 64- or 128-tiles or whole 32-tile panels and
-  // BF16x3 ones in 128 x 64 tiles, without a split, form the previous step's
-  // trace themselves (every block sums the stored diagonal,
-  // block 0 stores the scalars), so the trace pass runs once per call, after
-  // the last step; the sink and step count alternate between the scalar
-  // pairs by step parity (as for the unfolded steps)
-  bool fused_tr = false;
-  if constexpr (sizeof(T) == 4) {
-    if (c->precision == QME_FP32 && c->tile1 != 32) {
-      CgemmArgs<T> probe{u_re, u_im, x_re, x_im, x_re, x_im, y_re, y_im, c->ld, T(1), T(1)};
-      plan_product<T>(c, probe, c->tile1, false, area, nullptr, 0);
-      fused_tr = probe.split <= 1;
-    }
-    // (and FP32 32-tile first products that load whole panels)
-    if (c->precision == QME_FP32 && c->tile1 == 32 && c->ld <= kPanelLd && c->direct != 0)
-      fused_tr = true;
-    // (and BF16x3 first products on 128 x 64 tiles)
-    if (c->precision == QME_BF16X3) {
-      CgemmArgs<T> probe{u_re, u_im, x_re, x_im, x_re, x_im, y_re, y_im, c->ld, T(1), T(1)};
-      plan_product<T>(c, probe, plan_tile1(c), false, area, nullptr, 0);
-      fused_tr = wide_first(c, probe);
-    }
-  }
+  const bool fused_tr = trace_in_first_product<T>(c, area);
   for (int64_t k = 0; k < n_steps; ++k) {
     CgemmArgs<T> g1{u_re, u_im, x_re, x_im, x_re, x_im, y_re, y_im, c->ld, T(1), T(1)};
     if (k > 0 && fused_tr) {
@@ -429,7 +492,8 @@ static qme_status step_impl(qme_ctx *c, void *state, int64_t n_steps, void *ws,
   const TimerScope timer_scope;
   const size_t pe = plane_elems(c);
   if (!uses_small_path(c) && uses_fold(c)) {
-    hipError_t e = fold_steps<T>(c, state, n_steps, ws, s);
+    hipError_t e = uses_series(c) ? series_fold_steps<T>(c, state, n_steps, ws, s)
+                                  : fold_steps<T>(c, state, n_steps, ws, s);
     if (e != hipSuccess) {
       set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
       return QME_E_DEVICE;
@@ -534,6 +598,47 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
     HIP_OK(hipStreamSynchronize(s));
   }
   const int64_t n = c->n;
+  {
+    const SeriesPlan sp = plan_series(c->h, c->model.dt, c->precision == QME_FP64,
+                                      series_slices_per_wave(n));
+    if (sp.ok && n <= kSeriesMaxN) {
+      // one allocation and one copy: phases, values, neighbours, slots, slices
+      std::vector<char> tab;
+      auto put = [&](size_t bytes) {
+        const size_t at = tab.size();
+        tab.resize(at + align256(bytes));
+        return at;
+      };
+      const size_t o_ph = put(2 * sizeof(double) * size_t(n)), o_val = put(size_t(c->elem) * sp.val.size()),
+                   o_at = put(sizeof(int32_t) * sp.slot.size()), o_col = put(sizeof(int32_t) * sp.slot_col.size()),
+                   o_off = put(sizeof(int32_t) * sp.slice_off.size());
+      for (int64_t u = 0; u < n; ++u) {
+        double *ph = reinterpret_cast<double *>(tab.data() + o_ph) + 2 * u;
+        ph[0] = sp.phase_re[size_t(u)];
+        ph[1] = sp.phase_im[size_t(u)];
+      }
+      for (size_t e = 0; e < sp.val.size(); ++e) {
+        reinterpret_cast<int32_t *>(tab.data() + o_at)[e] = sp.slot[e] * series_slot_bytes(n);
+        if (c->elem == 8) reinterpret_cast<double *>(tab.data() + o_val)[e] = sp.val[e];
+        else reinterpret_cast<float *>(tab.data() + o_val)[e] = float(sp.val[e]);
+      }
+      std::copy(sp.slot_col.begin(), sp.slot_col.end(), reinterpret_cast<int32_t *>(tab.data() + o_col));
+      std::copy(sp.slice_off.begin(), sp.slice_off.end(), reinterpret_cast<int32_t *>(tab.data() + o_off));
+      HIP_OK(hipMalloc(&c->s_tables, tab.size()));
+      HIP_OK(hipMemcpy(c->s_tables, tab.data(), tab.size(), hipMemcpyHostToDevice));
+      char *t = static_cast<char *>(c->s_tables);
+      c->s_phase = reinterpret_cast<double *>(t + o_ph);
+      c->s_val = t + o_val;
+      c->s_at = reinterpret_cast<int32_t *>(t + o_at);
+      c->s_col = reinterpret_cast<int32_t *>(t + o_col);
+      c->s_off = reinterpret_cast<int32_t *>(t + o_off);
+      static_assert(kSeriesMaxOrder == kMaxSeriesOrder, "the plan's orders fit the passes");
+      c->series_order = sp.order;
+      c->series_faster = sp.faster;
+      for (int k = 1; k <= sp.order; ++k) c->series_ratio[k] = sp.coef[size_t(k)] / sp.coef[size_t(k) - 1];
+      c->series_phase = sp.has_phase;
+    }
+  }
   HIP_OK(hipMalloc(&c->d, sizeof(double) * n));
   HIP_OK(hipMalloc(&c->leak, sizeof(double) * n));
   HIP_OK(hipMalloc(&c->diag, sizeof(double) * (n + 8)));
@@ -930,6 +1035,8 @@ extern "C" qme_status qme_subspace(const qme_ctx *parent, const int32_t *keep, i
   st = finish_context(c.get(), parent->precision, hip_stream);
   if (st != QME_OK) return st;
   c->tail_split = parent->tail_split;
+  c->split_asked = parent->split_asked;
+  c->products = parent->products == 1 && c->series_order == 0 ? -1 : parent->products;
   c->fused = parent->fused;
   c->parent_n = parent->n;
   c->parent_ld = parent->ld;
@@ -1320,6 +1427,20 @@ extern "C" qme_status qme_set_split(qme_ctx *c, int32_t enable) {
   if (enable != 0 && enable != 1) { set_error("enable must be 0 or 1"); return QME_E_ARG; }
   c->drop_graphs();
   c->tail_split = enable != 0;
+  c->split_asked = enable != 0;
+  return QME_OK;
+}
+
+extern "C" qme_status qme_set_products(qme_ctx *c, int32_t form) {
+  set_error("");
+  if (!c) { set_error("ctx is NULL"); return QME_E_ARG; }
+  if (form < -1 || form > 1) { set_error("form must be -1, 0 or 1"); return QME_E_ARG; }
+  if (form == 1 && c->series_order == 0) {
+    set_error("this context's propagator has no series form");
+    return QME_E_UNSUPPORTED;
+  }
+  c->drop_graphs();
+  c->products = form;
   return QME_OK;
 }
 
@@ -1440,7 +1561,7 @@ qme_ctx::~qme_ctx() {
                   (void *)csr_gamma, (void *)csr_channel, (void *)loff_row, (void *)loff_col,
                   (void *)loff_val})
     if (p) (void)hipFree(p);
-  for (void *p : {du_re, du_im, du_split, (void *)parent_keep, (void *)d, (void *)leak, (void *)trw, (void *)diag, (void *)pi, (void *)cg,
+  for (void *p : {du_re, du_im, du_split, s_tables, (void *)parent_keep, (void *)d, (void *)leak, (void *)trw, (void *)diag, (void *)pi, (void *)cg,
                   (void *)tau, (void *)ca, (void *)upi, (void *)uc, (void *)ada, (void *)arrival_of,
                   (void *)h_ptr, (void *)h_col, (void *)h_val, (void *)t_row, (void *)t_col,
                   (void *)t_val})

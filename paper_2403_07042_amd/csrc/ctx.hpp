@@ -24,6 +24,8 @@ struct qme_ctx {
   int64_t n = 0, ld = 0;
   int tile1 = 64, tile2 = 64;         // tiles of the two products of a step
   bool tail_split = true;             // qme_set_split
+  bool split_asked = false;           // qme_set_split(ctx, 1) was called
+  int products = -1;                  // qme_set_products (-1 auto, 0 dense, 1 series)
   bool fused = true;                  // qme_set_fused (single-workgroup path, n <= 32)
   bool fold = true;                   // qme_set_fold (decoherence folded into the products)
   int direct = -1;                    // qme_set_direct_loads (-1 auto, 0 off, 1 on)
@@ -41,6 +43,15 @@ struct qme_ctx {
   // device tables (owned)
   void *du_re = nullptr, *du_im = nullptr;   // dU planes, ld x ld, storage type
   void *du_split = nullptr;                  // BF16X3: dU as six bf16 planes (split once)
+  // the propagator as a series (plan_series); series_order 0: none
+  int series_order = 0;
+  bool series_faster = false;                // than the dense products (the default's choice)
+  double series_ratio[qme::kSeriesMaxOrder + 1] = {};
+  bool series_phase = false;                 // the components' shifts differ
+  void *s_tables = nullptr;                  // owns the tables of the series:
+  int32_t *s_col = nullptr, *s_off = nullptr, *s_at = nullptr;
+  void *s_val = nullptr;                     // storage type
+  double *s_phase = nullptr;                 // [n][2]
   double *d = nullptr, *leak = nullptr, *diag = nullptr;
   double *trw = nullptr;              // trace weights (DissArgs::trw)
   int32_t *pi = nullptr;
@@ -150,6 +161,32 @@ template <typename T>
 // the scalars from slot pair `parity` and writing them to the other one.
 hipError_t step_once(qme_ctx *c, const void *in, void *out, void *y, void *z, hipStream_t s,
                      void *split_area = nullptr, int parity = -1);
+// Whether the steps apply the propagator by its series (series_tile.hpp) or
+// multiply by the dense dU.
+bool uses_series(const qme_ctx *c);
+// A row pass of the context's series (sign 1: conj(U), -1: U); phase: with the
+// whole phase of the propagator (a step of a density matrix needs only the
+// phase between components).
+template <typename T>
+SeriesArgs<T> series_args(const qme_ctx *c, const T *x_re, const T *x_im, T *o_re, T *o_im,
+                          int sign, bool phase) {
+  SeriesArgs<T> a{};
+  a.x_re = x_re;
+  a.x_im = x_im;
+  a.o_re = o_re;
+  a.o_im = o_im;
+  a.ld = c->ld;
+  a.n = c->n;
+  a.slot_col = c->s_col;
+  a.slice_off = c->s_off;
+  a.entry_at = c->s_at;
+  a.entry_val = static_cast<const T *>(c->s_val);
+  a.order = c->series_order;
+  a.sign = sign;
+  for (int k = 1; k <= c->series_order; ++k) a.ratio[k] = c->series_ratio[k];
+  a.phase = phase || c->series_phase ? c->s_phase : nullptr;
+  return a;
+}
 bool uses_small_path(const qme_ctx *c);
 bool uses_fold(const qme_ctx *c);
 // Whether the unfolded step forms the trace inside the decoherence pass

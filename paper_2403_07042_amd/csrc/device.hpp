@@ -373,4 +373,43 @@ template <typename T>
 hipError_t launch_set_diag(T *x_re, T *x_im, int64_t ld, int64_t n, const double *o,
                            hipStream_t s);
 
+// One row pass of the rotation by the propagator's series (series_tile.hpp):
+// each row x of X becomes conj(U) x (sign = 1) or U x (sign = -1).
+enum { kSeriesFirst = 0, kSeriesLower = 1, kSeriesFold = 2 };
+constexpr int kSeriesMaxOrder = 24;   // as kMaxSeriesOrder of the plan
+constexpr int64_t kSeriesMaxN = 8192;   // the rows of a workgroup fit its LDS
+template <typename T>
+struct SeriesArgs {
+  const T *x_re, *x_im;      // ld x ld, rows and columns < n read
+  T *o_re, *o_im;
+  int64_t ld, n;
+  // K dt (K = H less the shift): slot s holds state slot_col[s]; the entries
+  // of the 64 slots of slice q are those at [e * 64 + lane], slice_off[q] <= e
+  // < slice_off[q + 1] (rows shorter than the slice's longest: value 0):
+  // the neighbour's byte offset in a plane of LDS, and the value
+  const int32_t *slot_col, *slice_off, *entry_at;
+  const T *entry_val;
+  int32_t order, sign;
+  double ratio[kSeriesMaxOrder + 1];   // [1 .. order]: the series' coefficient ratios
+  const double *phase;       // e^{i shift dt} - 1 per state (re, im); nullptr: 0
+  int32_t groups = 0;        // row groups (set by the launcher)
+  // kSeriesFirst: the previous step's trace formed beside the pass (as
+  // CgemmArgs::tr_*, scalar slots 0)
+  const double *tr_zdiag = nullptr, *tr_w = nullptr, *tr_leak = nullptr;
+  double *tr_aux = nullptr;
+  double tr_dt = 0.0;
+  const double *scale = nullptr;   // kSeriesFold: the previous step's factor (nullptr: 1)
+  // kSeriesFold (as CgemmArgs::fold_*)
+  const double *fold_d = nullptr;
+  double fold_dt = 0.0;
+  double *zdiag = nullptr;
+};
+// After the last folded step of a call: the state *= *factor, exactly Hermitian.
+template <typename T>
+hipError_t launch_series_close(T *re, T *im, int64_t ld, int64_t n, const double *factor, hipStream_t s);
+int series_slot_bytes(int64_t n);        // LDS bytes per plane of one state of a workgroup's rows
+int series_slices_per_wave(int64_t n);   // slices of 64 states that a wave takes
+template <typename T>
+hipError_t launch_series_pass(const SeriesArgs<T> &a, int mode, hipStream_t s);
+
 }  // namespace qme

@@ -48,7 +48,8 @@ __device__ __forceinline__ void zlower(const DissArgs<T> &p, int64_t a, int64_t 
 // One workgroup of NT threads: FP64 trace of rho_d, lost probability,
 // sink and renormalisation factor of one step (see the file comment).
 // Returns the factor to every thread; `write`: store the step's scalars.
-template <typename T, int NT>
+// PART: the workgroup may have more than NT threads; the first NT form the sums.
+template <typename T, int NT, bool PART = false>
 __device__ __forceinline__ double trace_body(const DissArgs<T> &p, double *s_tr, double *s_lost,
                                              double *s_rot, bool write = true) {
   // tr rho_d = sum_u rho_d[u,u] = sum_w trw[w] Z[w,w]: the jump terms
@@ -95,7 +96,9 @@ __device__ __forceinline__ double trace_body(const DissArgs<T> &p, double *s_tr,
       }
     }
   };
-  if (p.zdiag)
+  if (PART && tid >= NT) {
+    // (only takes part in the barriers)
+  } else if (p.zdiag)
     sums([&](int64_t u) { return p.zdiag[u]; });
   else
     sums([&](int64_t u) { return double(p.z_re[u * p.ld + u]); });
@@ -106,7 +109,7 @@ __device__ __forceinline__ double trace_body(const DissArgs<T> &p, double *s_tr,
     lost += __shfl_xor(lost, off);
     rot += __shfl_xor(rot, off);
   }
-  if ((tid & 63) == 0) {
+  if ((tid & 63) == 0 && (!PART || tid < NT)) {
     s_tr[tid >> 6] = tr;
     s_lost[tid >> 6] = lost;
     s_rot[tid >> 6] = rot;

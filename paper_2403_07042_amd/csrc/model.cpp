@@ -754,6 +754,163 @@ bool propagator_increment(const Model &m, const Csr &h, std::vector<double> &re,
   return true;
 }
 
+// ------------------------------------------------------------ series
+
+std::vector<double> series_coefficients(double theta, double tol) {
+  // e^{i theta u} = sum_k (2 - [k = 0]) i^k J_k(theta) T_k(u) on |u| <= 1, cut
+  // after order m (the rest is below 4 (theta / 2)^(m+1) / (m+1)! for theta <=
+  // 1, with c_0 set to 1) and written in powers of z = i theta u.
+  if (!(theta >= 0.0) || theta > 1.0) return {};
+  int m = 0;
+  double rest = 2.0 * theta;   // 4 (theta / 2)^(m+1) / (m+1)!
+  while (m < 1 || rest > tol) {
+    if (++m > kMaxSeriesOrder) return {};
+    rest *= 0.5 * theta / double(m + 1);
+  }
+  std::vector<long double> c(size_t(m) + 1, 0.0L), t0(size_t(m) + 1, 0.0L), t1(t0), t2(t0);
+  // t_k: T_k(u) in powers of u, over theta^power; i^k T_k(u) has only the
+  // powers of k's parity, and u^j i^k = z^j i^(k-j) / theta^j with i^(k-j) real
+  t0[0] = 1.0L;
+  t1[1] = 1.0L;
+  const long double h = 0.5L * (theta > 0.0 ? (long double)theta : 1e-30L);
+  for (int k = 0; k <= m; ++k) {
+    const std::vector<long double> &t = k == 0 ? t0 : t1;
+    long double lead = 1.0L, bessel = 0.0L;
+    for (int j = 1; j <= k; ++j) lead *= h / j;          // (theta / 2)^k / k!
+    long double term = lead;
+    for (int j = 0; j < 24; ++j) {
+      bessel += term;
+      term *= -h * h / ((long double)(j + 1) * (long double)(j + 1 + k));
+    }
+    long double power = 1.0L;                            // theta^j
+    for (int j = 0; j <= k; ++j) {
+      if ((k - j) % 2 == 0) {
+        const long double sign = ((k - j) / 2) % 2 == 0 ? 1.0L : -1.0L;
+        c[size_t(j)] += (k == 0 ? 1.0L : 2.0L) * bessel * sign * t[size_t(j)] / power;
+      }
+      power *= 2.0L * h;
+    }
+    if (k >= 1) {                                        // T_{k+1} = 2 u T_k - T_{k-1}
+      for (int j = 0; j <= m; ++j) t2[size_t(j)] = (j > 0 ? 2.0L * t1[size_t(j) - 1] : 0.0L) - t0[size_t(j)];
+      t0 = t1;
+      t1 = t2;
+    }
+  }
+  std::vector<double> out(c.begin(), c.end());
+  out[0] = 1.0;
+  return out;
+}
+
+SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
+  SeriesPlan p;
+  const int64_t n = h.n;
+  if (n <= 32) return p;   // the single-workgroup path's sizes
+  // connected components of the couplings
+  std::vector<int32_t> root(static_cast<size_t>(n));
+  for (int64_t i = 0; i < n; ++i) root[size_t(i)] = int32_t(i);
+  auto find = [&](int32_t x) {
+    while (root[size_t(x)] != x) x = root[size_t(x)] = root[size_t(root[size_t(x)])];
+    return x;
+  };
+  std::vector<double> diag(static_cast<size_t>(n), 0.0);
+  for (int64_t i = 0; i < n; ++i)
+    for (int64_t e = h.ptr[i]; e < h.ptr[i + 1]; ++e) {
+      if (h.col[e] == i) {
+        diag[size_t(i)] += h.val[e];
+      } else if (h.val[e] != 0.0) {
+        const int32_t a = find(int32_t(i)), b = find(h.col[e]);
+        if (a != b) root[size_t(std::max(a, b))] = std::min(a, b);
+      }
+    }
+  std::vector<double> lo(static_cast<size_t>(n), HUGE_VAL), hi(static_cast<size_t>(n), -HUGE_VAL);
+  for (int64_t i = 0; i < n; ++i) {
+    const size_t c = size_t(find(int32_t(i)));
+    lo[c] = std::min(lo[c], diag[size_t(i)]);
+    hi[c] = std::max(hi[c], diag[size_t(i)]);
+  }
+  std::vector<std::vector<std::pair<int32_t, double>>> rows(static_cast<size_t>(n));
+  p.phase_re.resize(size_t(n));
+  p.phase_im.resize(size_t(n));
+  double first_shift = 0.0;
+  for (int64_t i = 0; i < n; ++i) {
+    const size_t c = size_t(find(int32_t(i)));
+    const double shift = 0.5 * (lo[c] + hi[c]);
+    if (i == 0) first_shift = shift;
+    if (shift != first_shift) p.has_phase = true;
+    // e^{ix} - 1 without cancellation: -2 sin^2(x / 2) + i sin x
+    const double s = std::sin(0.5 * shift * dt);
+    p.phase_re[size_t(i)] = -2.0 * s * s;
+    p.phase_im[size_t(i)] = std::sin(shift * dt);
+    double sum = 0.0;
+    auto &row = rows[size_t(i)];
+    if (diag[size_t(i)] != shift) row.push_back({int32_t(i), (diag[size_t(i)] - shift) * dt});
+    for (int64_t e = h.ptr[i]; e < h.ptr[i + 1]; ++e)
+      if (h.col[e] != i && h.val[e] != 0.0) row.push_back({h.col[e], h.val[e] * dt});
+    for (const auto &e : row) sum += std::fabs(e.second);
+    p.theta = std::max(p.theta, sum);
+  }
+  p.coef = series_coefficients(p.theta, fp64 ? 1e-18 : 1e-12);
+  p.order = int(p.coef.size()) - 1;
+  size_t nnz = 0;
+  for (const auto &row : rows) nnz += row.size();
+  // A step's series costs order (entries per row + 3) LDS accesses per element,
+  // its dense products N multiply-adds.  Measured (MI355X, us per step, series
+  // against dense): N = 2048 lattice (cost 18) 44 / 611 FP32 and 95 / 1296
+  // FP64, N = 144 TCH (25) 16.1 / 20.6, N = 64 TCH (18) 13.4 / 14.2, but N = 64
+  // hydrogen bond (43) 16.5 / 15.5 and N = 48 (54) 19.0 / 16.4.  N <= 32 has
+  // the single-workgroup path.
+  const double cost = double(p.order) * (double(nnz) / double(std::max<int64_t>(n, 1)) + 3.0);
+  p.ok = p.order >= 1 && cost < 2.0 * double(n);
+  p.faster = p.ok && cost < 0.6 * double(n);
+  if (!p.ok) return p;
+  // slots in decreasing row length, so that the 64 rows of a slice are alike
+  p.slot_col.resize(size_t(n));
+  for (int64_t i = 0; i < n; ++i) p.slot_col[size_t(i)] = int32_t(i);
+  std::stable_sort(p.slot_col.begin(), p.slot_col.end(), [&](int32_t a, int32_t b) {
+    return rows[size_t(a)].size() > rows[size_t(b)].size();
+  });
+  // wave w of a pass takes `per_wave` slices in a row: the sorted slices are
+  // dealt to the waves, so that the long ones spread over them
+  {
+    const int64_t full = n / 64;   // whole slices; the states left over stay last
+    const int64_t waves = (full + per_wave - 1) / per_wave;
+    std::vector<int32_t> dealt;
+    dealt.reserve(size_t(n));
+    for (int64_t w = 0; w < waves; ++w)
+      for (int64_t q = w; q < full; q += waves)
+        dealt.insert(dealt.end(), p.slot_col.begin() + q * 64, p.slot_col.begin() + q * 64 + 64);
+    dealt.insert(dealt.end(), p.slot_col.begin() + full * 64, p.slot_col.end());
+    p.slot_col = std::move(dealt);
+  }
+  std::vector<int32_t> slot_of(static_cast<size_t>(n));
+  for (int64_t s = 0; s < n; ++s) slot_of[size_t(p.slot_col[size_t(s)])] = int32_t(s);
+  p.slice_off.assign(1, 0);
+  for (int64_t q = 0; q * 64 < n; ++q) {
+    size_t longest = 0;
+    for (int64_t s = q * 64; s < std::min(n, q * 64 + 64); ++s)
+      longest = std::max(longest, rows[size_t(p.slot_col[size_t(s)])].size());
+    for (size_t e = 0; e < longest; ++e)
+      for (int64_t s = q * 64; s < q * 64 + 64; ++s) {
+        int32_t to = int32_t(s < n ? s : 0);
+        double v = 0.0;
+        if (s < n) {
+          const auto &row = rows[size_t(p.slot_col[size_t(s)])];
+          if (e < row.size()) {
+            to = slot_of[size_t(row[e].first)];
+            v = row[e].second;
+          }
+        }
+        p.slot.push_back(to);
+        p.val.push_back(v);
+      }
+    p.slice_off.push_back(p.slice_off.back() + int32_t(longest));
+  }
+  // (a pass loads the first few entries of a slice whatever their number)
+  p.slot.resize(p.slot.size() + 8 * 64, 0);
+  p.val.resize(p.val.size() + 8 * 64, 0.0);
+  return p;
+}
+
 // ------------------------------------------------------------ Frechet
 
 // y = (-i tau H) x for complex planar dense x (rows), H sparse real symmetric.

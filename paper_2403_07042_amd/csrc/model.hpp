@@ -158,6 +158,30 @@ bool propagator_increment(const Model &m, const Csr &h, std::vector<double> &re,
                           std::vector<std::vector<double>> *levels = nullptr,
                           int *squarings = nullptr);
 
+// The propagator as a series: U = e^{-i shift dt} e^{-i K dt}, K = H - shift,
+// the shift constant on each connected component of H (the middle of the
+// component's diagonal, so that K's norm is small).  Rows of K dt in slots of
+// 64 (sliced ELL); a shorter row is filled with zero entries on its own slot.
+struct SeriesPlan {
+  bool ok = false;                  // the plan exists (H sparse, |K dt| <= 1)
+  bool faster = false;              // and its passes are expected to beat the dense products
+  int order = 0;
+  double theta = 0.0;               // |K dt|_1
+  std::vector<double> coef;         // e^z = sum_k coef[k] z^k, k <= order
+  bool has_phase = false;           // the shift differs between components
+  std::vector<int32_t> slot_col;    // per slot: its state (n slots)
+  std::vector<int32_t> slice_off;   // per slice of 64 slots
+  std::vector<int32_t> slot;        // per entry (slice, entry, lane): the neighbour's slot
+  std::vector<double> val;
+  std::vector<double> phase_re, phase_im;   // e^{i shift dt} - 1 per state
+};
+constexpr int kMaxSeriesOrder = 24;
+// Coefficients of e^z in powers of z for z = i y, |y| <= theta <= 1: the
+// Chebyshev series cut where the rest is below tol (a term or two fewer than
+// Taylor's series needs).  Empty: theta out of range.
+std::vector<double> series_coefficients(double theta, double tol);
+SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave);
+
 // W = L(A, G), the Frechet derivative of exp at A = -i H dt applied to G
 // in its adjoint form tr(G L(A, E)) = tr(L(A, G) E); G and W are complex
 // planar n x n (FP64, row-major).

@@ -1,0 +1,162 @@
+// Launchers of the series row passes (series_tile.hpp).
+#include "series_tile.hpp"
+
+#include <algorithm>
+
+namespace qme {
+
+// as the trace pass, so that the factor is bitwise the same
+static constexpr int kSeriesTraceThreads = 256;
+
+// The first pass of a folded step also forms the previous step's trace, in one
+// further workgroup that runs beside the others (tr_zdiag); the factor it
+// stores is applied by the step's second pass, which the stream orders after.
+template <typename T, int R, int S, int NT, int MODE>
+__global__ __launch_bounds__(NT, 4) void series_pass_kernel(SeriesArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  if constexpr (MODE == kSeriesFirst) {
+    if (a.tr_zdiag && blockIdx.x == gridDim.x - 1) {
+      DissArgs<T> d{};
+      d.n = a.n;
+      d.dt = a.tr_dt;
+      d.trw = a.tr_w;
+      d.leak = a.tr_leak;
+      d.zdiag = a.tr_zdiag;
+      d.aux_in = d.aux_out = a.tr_aux;
+      double *st = reinterpret_cast<double *>(lds);
+      constexpr int W = kSeriesTraceThreads / 64;
+      trace_body<T, kSeriesTraceThreads, true>(d, st, st + W, st + 2 * W);
+      return;
+    }
+  }
+  const int group = series_group(int(blockIdx.x), a.groups);
+  if (group >= a.groups) return;
+  series_rows<T, R, S, NT, MODE>(a, group, lds);
+}
+
+// The closing pass of a call of folded series steps: X *= factor (FP64) with
+// the upper triangle taken from the lower, so the stored state is exactly
+// Hermitian.  One workgroup per 32 x 32 tile on or below the diagonal, its
+// mirror staged through LDS (32 x 33 elements).
+template <typename T>
+__global__ __launch_bounds__(256) void series_close_kernel(T *re, T *im, int64_t ld, int64_t n,
+                                                           const double *factor) {
+  __shared__ T s_re[32][33], s_im[32][33];
+  int bi = int((sqrtf(8.0f * float(blockIdx.x) + 1.0f) - 1.0f) * 0.5f);
+  while ((bi + 1) * (bi + 2) / 2 <= int(blockIdx.x)) ++bi;
+  while (bi * (bi + 1) / 2 > int(blockIdx.x)) --bi;
+  const int bj = int(blockIdx.x) - bi * (bi + 1) / 2;
+  const double f = *factor;
+  const int c = int(threadIdx.x) & 31, r0 = int(threadIdx.x) >> 5;
+  T x_re[4], x_im[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t u = std::min<int64_t>(int64_t(bi) * 32 + r0 + 8 * i, n - 1);
+    const int64_t v = std::min<int64_t>(int64_t(bj) * 32 + c, n - 1);
+    x_re[i] = re[u * ld + v];
+    x_im[i] = im[u * ld + v];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = r0 + 8 * i;
+    const int64_t u = int64_t(bi) * 32 + r, v = int64_t(bj) * 32 + c;
+    const T a = T(f * double(x_re[i])), b = u == v ? T(0) : T(f * double(x_im[i]));
+    s_re[r][c] = a;
+    s_im[r][c] = b;
+    if (u < n && v <= u) {
+      re[u * ld + v] = a;
+      im[u * ld + v] = b;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = r0 + 8 * i;   // row of the mirror: a column of the tile
+    const int64_t u = int64_t(bj) * 32 + r, v = int64_t(bi) * 32 + c;
+    if (v < n && u < v) {
+      re[u * ld + v] = s_re[c][r];
+      im[u * ld + v] = -s_im[c][r];
+    }
+  }
+}
+
+namespace {
+
+template <typename T, int R, int S, int NT, int MODE>
+hipError_t launch_one(const SeriesArgs<T> &in, hipStream_t s) {
+  SeriesArgs<T> a = in;
+  a.groups = int32_t((a.n + R - 1) / R);
+  constexpr size_t lds = size_t(2) * S * NT * R * sizeof(T);   // up to all 160 KB
+  const auto kernel = series_pass_kernel<T, R, S, NT, MODE>;
+  if (lds > 48 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  const unsigned grid = unsigned((a.groups + 7) / 8 * 8) + (MODE == kSeriesFirst && a.tr_zdiag ? 1 : 0);
+  return launch_kernel(kernel, dim3(grid), dim3(NT), uint32_t(lds), s, a);
+}
+
+template <typename T, int R, int S, int NT>
+hipError_t launch_mode(const SeriesArgs<T> &a, int mode, hipStream_t s) {
+  switch (mode) {
+    case kSeriesFirst: return launch_one<T, R, S, NT, kSeriesFirst>(a, s);
+    case kSeriesLower: return launch_one<T, R, S, NT, kSeriesLower>(a, s);
+    case kSeriesFold: return launch_one<T, R, S, NT, kSeriesFold>(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+// The shape of a pass: bytes of a unit, slices per wave, threads.  A workgroup
+// holds its rows in LDS (2 x 64 states x slices x waves x bytes: up to all of
+// 160 KB) and in registers (128 at four waves per SIMD), so the rows get fewer
+// as N grows.
+struct SeriesShape {
+  int bytes, slices, threads;
+};
+static SeriesShape series_shape(int64_t n) {
+  if (n <= 256) return {16, 1, 256};
+  if (n <= 512) return {16, 2, 256};
+  if (n <= 1024) return {16, 2, 512};
+  if (n <= 2048) return {32, 2, 1024};
+  if (n <= 4096) return {16, 4, 1024};
+  if (n <= 5120) return {16, 5, 1024};
+  return {8, 8, 1024};
+}
+
+int series_slot_bytes(int64_t n) { return std::min(series_shape(n).bytes, 16); }
+int series_slices_per_wave(int64_t n) { return series_shape(n).slices; }
+
+template <typename T>
+hipError_t launch_series_pass(const SeriesArgs<T> &a, int mode, hipStream_t s) {
+  constexpr int E = int(sizeof(T));
+  if (a.n < 1 || a.n > kSeriesMaxN || a.ld < a.n || a.order < 1 || a.order > kSeriesMaxOrder)
+    return hipErrorInvalidValue;
+  const SeriesShape f = series_shape(a.n);
+  // (W^dag takes whole blocks of four units by R)
+  if ((a.n + 3) / 4 * 4 * ((a.n * E + f.bytes - 1) / f.bytes) * (f.bytes / E) > a.ld * a.ld)
+    return hipErrorInvalidValue;
+  if (f.bytes == 32) return launch_mode<T, 32 / E, 2, 1024>(a, mode, s);
+  if (f.bytes == 8) return launch_mode<T, 8 / E, 8, 1024>(a, mode, s);
+  if (f.slices == 1) return launch_mode<T, 16 / E, 1, 256>(a, mode, s);
+  if (f.slices == 2 && f.threads == 256) return launch_mode<T, 16 / E, 2, 256>(a, mode, s);
+  if (f.slices == 2) return launch_mode<T, 16 / E, 2, 512>(a, mode, s);
+  if (f.slices == 4) return launch_mode<T, 16 / E, 4, 1024>(a, mode, s);
+  return launch_mode<T, 16 / E, 5, 1024>(a, mode, s);
+}
+
+template <typename T>
+hipError_t launch_series_close(T *re, T *im, int64_t ld, int64_t n, const double *factor, hipStream_t s) {
+  const int64_t t = (n + 31) / 32;
+  return launch_kernel(series_close_kernel<T>, dim3(unsigned(t * (t + 1) / 2)), dim3(256), 0, s, re, im,
+                       ld, n, factor);
+}
+
+template hipError_t launch_series_close<float>(float *, float *, int64_t, int64_t, const double *, hipStream_t);
+template hipError_t launch_series_close<double>(double *, double *, int64_t, int64_t, const double *, hipStream_t);
+template hipError_t launch_series_pass<float>(const SeriesArgs<float> &, int, hipStream_t);
+template hipError_t launch_series_pass<double>(const SeriesArgs<double> &, int, hipStream_t);
+
+}  // namespace qme

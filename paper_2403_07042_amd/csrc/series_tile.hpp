@@ -1,0 +1,331 @@
+// Row passes of the rotation rho_u = U rho U^dag with U = exp(-i H dt) applied
+// by its Taylor series instead of as a dense matrix.
+//
+// H is sparse (a few couplings per state), so U v needs the series' few terms
+// of a sparse product where the dense product needs N multiply-adds per
+// element.  U is symmetric (H is real symmetric), so with
+//   R(X) = X conj(U)          (each row x of X by itself: conj(U) x)
+// the rotation is two row passes with a conjugate transpose between:
+//   W = R(rho),  rho_u = R(W^dag)   (= W^dag U^dag = U rho^dag U^dag),
+// the first pass writing W^dag.  Both passes read whole rows (contiguous).
+//
+// One workgroup takes R rows.  The rows' elements at one basis state form one
+// unit of 16 (or 8) bytes per plane, so a lane gathers a neighbouring state of
+// all its rows with one LDS read per plane.  The series runs in Horner form
+//   v <- x + (A v) / k,  k = order .. 2,   delta = A v,   result = x + delta,
+// A = +-i K dt with K = H less a shift that is constant on each connected
+// component of H (it commutes with H; e^{-+i shift dt} is applied exactly, in
+// FP64, at the end).  v lives in LDS, x and the sums in registers: a term is
+// one gather sweep and two barriers.  (The coefficients are those of the
+// series economised on |K dt| <= theta, which needs a term or two less:
+// ratio[k] stands for 1 / k.)  x is added in FP64 and the result
+// rounded once.
+//
+// What bounds it: at N = 2048 a pass moves 33.5 MB in and 33.5 MB out (a copy of
+// that size takes 8.4 us) and reads 0.4 GB of LDS; its loads, terms and stores
+// run one after another in a workgroup, and the launch is one round of them.
+// Measured: 22.8 + 21.8 us FP32 (three terms) and 45.6 + 45.1 us FP64 (four),
+// against 387 + 224 and 844 + 452 us of the dense products.
+#pragma once
+
+#include <cstdint>
+
+#include "device.hpp"
+#include "dissipate_tile.hpp"
+
+namespace qme {
+
+// Workgroups are dealt to the XCDs round-robin.  Consecutive row groups go to
+// one XCD, so the R-element pieces of a line that the transposed writes leave
+// meet in that XCD's L2.
+__device__ __forceinline__ int series_group(int block, int groups) {
+  const int per = (groups + 7) >> 3;
+  return (block & 7) * per + (block >> 3);
+}
+
+template <typename T>
+__device__ __forceinline__ T series_fma(T a, T b, T c) {
+  if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, b, c);
+  else return __builtin_fma(a, b, c);
+}
+
+// W^dag between the two passes: element (c, r) in slot order, units of R
+// consecutive r of one c, the units of four c side by side and then the next
+// group of R r.  The first pass's workgroup (one group of R r, every c) writes,
+// and the second's (R of the c, every r) reads, whole pieces of four units (64
+// or 128 bytes).  A transposed row-major plane had it write single 16-byte
+// units, one request of the L2 each: 13 of the 31 us that the first pass took
+// at N = 2048.
+__device__ __forceinline__ int64_t series_unit(int c, int g, int groups) {
+  return (int64_t(c >> 2) * groups + g) * 4 + (c & 3);
+}
+
+// MODE kSeriesFirst: reads the state, writes W^dag in blocks (series_unit).
+// MODE kSeriesLower: reads those blocks, writes the rows of rho_u on and below
+// the diagonal.
+// MODE kSeriesFold: as kSeriesLower with the previous step's factor and the
+// decoherence factor applied, whole rows written, the diagonal before the
+// decoherence kept for the trace (CgemmArgs::fold_d).  Both triangles come
+// from their own rows here, so they agree to rounding only; the closing pass
+// of the call restores the exact symmetry (Herm commutes with every step).
+//
+// Factors near one are applied as x + (small terms), the small terms in the
+// storage type and their coefficients formed in FP64, so that a result is
+// rounded once, at the last addition.
+template <typename T, int R, int S, int NT, int MODE>
+__device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, unsigned char *lds) {
+  // (a batch's passes give each instance the bits of its own passes: the
+  // arithmetic must not depend on what the compiler fuses in each shape)
+#pragma clang fp contract(off)
+  typedef T unit __attribute__((ext_vector_type(R)));
+  // v in LDS: a unit's 16-byte parts (one or two) in planes of their own, so
+  // that lanes with neighbouring slots read without bank conflicts; the
+  // imaginary planes follow the real ones
+  constexpr int kPart = sizeof(unit) < 16 ? int(sizeof(unit)) : 16;
+  constexpr int P = int(sizeof(unit)) / kPart;
+  constexpr int E = R / P;
+  typedef T part __attribute__((ext_vector_type(E)));
+  constexpr int kPlane = S * NT * kPart;
+  auto put = [](unsigned char *base, int slot, const unit &re, const unit &im) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      part a, b;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        a[e] = re[p * E + e];
+        b[e] = im[p * E + e];
+      }
+      *reinterpret_cast<part *>(base + p * kPlane + slot * kPart) = a;
+      *reinterpret_cast<part *>(base + (P + p) * kPlane + slot * kPart) = b;
+    }
+  };
+  const int tid = int(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = int(a.n);
+  const int slots = (n + 63) & ~63;
+  const int groups = (n + R - 1) / R;
+  const int q0 = group * R;            // the rows: states of slots q0 .. q0 + R - 1
+  int row[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    row[r] = __builtin_amdgcn_readfirstlane(a.slot_col[min(q0 + r, n - 1)]);
+
+  // Wave w takes slices w S .. w S + S - 1 of 64 slots.  With one or two
+  // slices a wave keeps their first C entries in registers for all terms;
+  // with more it loads a slice's first C when the slice before it has used
+  // its own.  Further entries are loaded as they come.
+  constexpr int C = sizeof(T) == 4 ? 4 : 3;
+  constexpr int B = S <= 2 ? S : 1;
+  int off[S + 1];
+#pragma unroll
+  for (int s = 0; s <= S; ++s) off[s] = a.slice_off[min(wave * S + s, slots >> 6)];
+  struct Entries {
+    int32_t at[C];
+    T val[C];
+  };
+  Entries buf[B];
+  auto fetch = [&](Entries &to, int first) {
+    const int32_t *p = a.entry_at + int64_t(first) * 64;
+    const T *q = a.entry_val + int64_t(first) * 64;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      to.at[i] = p[unsigned(i * 64 + lane)];
+      to.val[i] = q[unsigned(i * 64 + lane)];
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < B; ++s) fetch(buf[s], off[s]);
+
+  // the rows, one state per lane.  A slot or row past the end repeats the
+  // last one: no entry reads it and it is not written.
+  unit x_re[S], x_im[S];
+  unsigned col[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) col[s] = unsigned(a.slot_col[unsigned(min((wave * S + s) * 64 + lane, n - 1))]);
+  if constexpr (MODE == kSeriesFirst) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const T *p_re = a.x_re + int64_t(row[r]) * a.ld, *p_im = a.x_im + int64_t(row[r]) * a.ld;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        x_re[s][r] = p_re[col[s]];
+        x_im[s][r] = p_im[col[s]];
+      }
+    }
+  } else {
+    unsigned at[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int slot = min((wave * S + s) * 64 + lane, n - 1);
+      at[s] = unsigned(series_unit(0, slot / R, groups)) * R + unsigned(slot % R);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int64_t o = series_unit(min(q0 + r, n - 1), 0, groups) * R;
+      const T *p_re = a.x_re + o, *p_im = a.x_im + o;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        x_re[s][r] = p_re[at[s]];
+        x_im[s][r] = p_im[at[s]];
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int slot = (wave * S + s) * 64 + lane;
+    put(lds, slot, x_re[s], x_im[s]);
+  }
+
+  unit t_re[S], t_im[S];
+  const T sgn = T(a.sign);
+  for (int k = a.order; k >= 1; --k) {
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) t_re[s][r] = t_im[s][r] = T(0);
+      auto add = [&](T val, int at) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          const part g_re = *reinterpret_cast<const part *>(lds + at + p * kPlane);
+          const part g_im = *reinterpret_cast<const part *>(lds + at + (P + p) * kPlane);
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            t_re[s][p * E + e] = series_fma<T>(val, g_re[e], t_re[s][p * E + e]);
+            t_im[s][p * E + e] = series_fma<T>(val, g_im[e], t_im[s][p * E + e]);
+          }
+        }
+      };
+      auto chunk = [&](const Entries &q, int cnt) {
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+          if (i < cnt) add(q.val[i], q.at[i]);
+      };
+      const int cnt = off[s + 1] - off[s];
+      Entries &own = buf[s % B];
+      const int next = off[(s + 1) % S];
+      chunk(own, cnt);
+      if constexpr (S <= 2) {
+        for (int e = C; e < cnt; e += C) {
+          Entries more;
+          fetch(more, off[s] + e);
+          chunk(more, cnt - e);
+        }
+      } else {
+        for (int e = C; e < cnt; e += C) {
+          fetch(own, off[s] + e);
+          chunk(own, cnt - e);
+        }
+        fetch(own, next);
+      }
+    }
+    if (k == 1) break;
+    __syncthreads();
+    const T w = sgn * T(a.ratio[k]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      unit n_re, n_im;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        n_re[r] = series_fma<T>(-w, t_im[s][r], x_re[s][r]);
+        n_im[r] = series_fma<T>(w, t_re[s][r], x_im[s][r]);
+      }
+      const int slot = (wave * S + s) * 64 + lane;
+      put(lds, slot, n_re, n_im);
+    }
+  }
+
+  // (the row passes hand their results to LDS, by state, so that the rows are
+  // written in order: the slots' order would leave parts of lines)
+  if constexpr (MODE != kSeriesFirst) __syncthreads();
+  const T w1 = sgn * T(a.ratio[1]);
+  double eps = 0.0;                    // the previous step's factor less 1
+  double row_d[R];
+  if constexpr (MODE == kSeriesFold) {
+    if (a.scale) eps = *a.scale - 1.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) row_d[r] = 0.5 * a.fold_dt * a.fold_d[row[r]];
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int slot = (wave * S + s) * 64 + lane;
+    if (slot >= n) continue;
+    const unsigned c = col[s];
+    T q_re = T(0), q_im = T(0);
+    if (a.phase) {
+      q_re = T(a.phase[2 * c]);
+      q_im = sgn * T(a.phase[2 * c + 1]);
+    }
+    double col_d = 0.0;
+    if constexpr (MODE == kSeriesFold) col_d = 0.5 * a.fold_dt * a.fold_d[c];
+    unit w_re, w_im;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const T xr = x_re[s][r], xi = x_im[s][r];
+      T dr = -w1 * t_im[s][r], di = w1 * t_re[s][r];   // result = x + d
+      if (a.phase) {   // (1 + q)(x + d)
+        const T yr = xr + dr, yi = xi + di;
+        dr = series_fma<T>(-q_im, yi, series_fma<T>(q_re, yr, dr));
+        di = series_fma<T>(q_im, yr, series_fma<T>(q_re, yi, di));
+      }
+      if constexpr (MODE == kSeriesFirst) {
+        w_re[r] = xr + dr;
+        w_im[r] = -(xi + di);
+      } else if constexpr (MODE == kSeriesLower) {
+        w_re[r] = xr + dr;
+        w_im[r] = xi + di;
+      } else {
+        // (1 + eps)(1 - phi)(x + d)
+        // (the trace is taken of the diagonal as it is stored)
+        if (unsigned(row[r]) == c && q0 + r < n)
+          a.zdiag[c] = double(xr + series_fma<T>(T(eps), xr + dr, dr));
+        const double phi = row_d[r] + col_d;
+        const T f = T(eps - phi - eps * phi);
+        w_re[r] = xr + series_fma<T>(f, xr + dr, dr);
+        w_im[r] = xi + series_fma<T>(f, xi + di, di);
+      }
+    }
+    if constexpr (MODE == kSeriesFirst) {
+      const int64_t u = series_unit(0, group, groups);
+      const unsigned o = unsigned(series_unit(slot, 0, groups));
+      (reinterpret_cast<unit *>(a.o_re) + u)[o] = w_re;
+      (reinterpret_cast<unit *>(a.o_im) + u)[o] = w_im;
+    } else {
+      put(lds, int(c), w_re, w_im);
+    }
+  }
+  if constexpr (MODE != kSeriesFirst) {
+    __syncthreads();
+    unit w_re[S], w_im[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const part a_re = *reinterpret_cast<const part *>(lds + (s * NT + tid) * kPart + p * kPlane);
+        const part a_im = *reinterpret_cast<const part *>(lds + (s * NT + tid) * kPart + (P + p) * kPlane);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          w_re[s][p * E + e] = a_re[e];
+          w_im[s][p * E + e] = a_im[e];
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (q0 + r >= n) break;
+      T *p_re = a.o_re + int64_t(row[r]) * a.ld, *p_im = a.o_im + int64_t(row[r]) * a.ld;
+      const int end = MODE == kSeriesFold ? n : row[r] + 1;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const unsigned c = unsigned(s * NT + tid);
+        if (int(c) < end) {
+          p_re[c] = w_re[s][r];
+          p_im[c] = w_im[s][r];
+        }
+      }
+    }
+  }
+}
+
+}  // namespace qme

@@ -1,0 +1,176 @@
+"""The propagator applied by its series (qme_set_products(ctx, 1)) against the
+dense products (0) and the oracle: the edges of the row passes' shapes, ragged
+sizes, components of H with different shifts, long and empty rows of H, the
+choice between the forms, and batches that mix them."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import evolve as ev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+P = pytest.importorskip("paper_2403_07042_amd")
+from paper_2403_07042_amd import _lib as L  # noqa: E402
+
+# the suite's tolerances against the oracle, relative to the largest element;
+# two forms that each meet it differ by at most twice as much
+TOL = {"fp64": 1e-12, "fp32": 1e-5, "bf16x3": 1e-4}
+
+
+def cavity_chain(n, dt=0.25, gamma=0.01):
+    """n cavities in a row with one photon among them, leaking at the ends."""
+    return dict(W.photon_lattice(n, 1, mu=0.2, g=0.0, gamma=0.0, dt=dt, atoms_per_site=0),
+                jumps=[(W.PHOTON_LEAK, 0, -1, gamma), (W.PHOTON_LEAK, n - 1, -1, gamma)])
+
+
+def random_model(n, degree, seed, dt=0.02, isolated=0):
+    """A general model: a random symmetric H with rows of about `degree` entries
+    (the first state coupled to many more) in two components of different
+    frequency, the last `isolated` states coupled to nothing, and a lowering
+    operator (the next state, the last one leaving the basis)."""
+    rng = np.random.default_rng(seed)
+    h = np.zeros((n, n))
+    half = n // 2
+    for lo, hi in ((0, half), (half, n - isolated)):
+        for _ in range((hi - lo) * degree // 2):
+            a, b = rng.integers(lo, hi, 2)
+            if a != b:
+                h[a, b] = h[b, a] = rng.uniform(0.02, 0.2)
+    h[0, 1:20] = h[1:20, 0] = 0.05
+    h += np.diag(np.where(np.arange(n) < half, 1.0, 3.0) + rng.uniform(0.0, 0.1, n))
+    r, c = np.nonzero(h)
+    src = list(range(n))
+    return {"general": True, "name": f"random_{n}", "n": n,
+            "h": (r.astype(np.int32), c.astype(np.int32), h[r, c]),
+            "jumps": [(0.01, src, src[1:] + [-1], [1.0] * n)], "dt": dt}
+
+
+def run(wl, precision, form, calls, rho0, fold=True):
+    sol = P.Solver(wl, precision)
+    sol.set_products(form)
+    sol.set_fold(fold)
+    sol.set_rho(rho0, sink=0.125)
+    for k in calls:
+        sol.step(k)
+    rho, sink = sol.get_rho()
+    _, trace, _ = sol.observe()
+    sol.close()
+    return rho, sink, trace
+
+
+def check(got, ref, precision):
+    tol = 2 * TOL[precision]
+    assert np.abs(got[0] - ref[0]).max() < tol * np.abs(ref[0]).max()
+    assert np.array_equal(got[0], got[0].conj().T)
+    assert abs(got[1] - ref[1]) < tol and abs(got[2] - (1.0 - got[1])) < max(1e-12, 0.1 * tol)
+
+
+SIZES = [33, 64, 65, 255, 256, 257, 511, 513, 1023, 1025, 2047, 2049]
+
+
+@pytest.mark.parametrize("fold", [True, False])
+@pytest.mark.parametrize("precision", ["fp32", "fp64", "bf16x3"])
+@pytest.mark.parametrize("n", SIZES)
+def test_shape_edges_against_dense(n, precision, fold):
+    wl = cavity_chain(n)
+    psi = W.haar_psi(n, 3)
+    rho0 = np.outer(psi, psi.conj())
+    print(f"series N={n} {precision} fold={fold}", flush=True)
+    check(run(wl, precision, 1, (3, 4), rho0, fold), run(wl, precision, 0, (3, 4), rho0, fold), precision)
+
+
+@pytest.mark.parametrize("n,precision", [(4095, "fp32"), (4097, "fp32"), (5120, "fp32"), (5121, "fp32"),
+                                         (4097, "fp64")])
+def test_large_shapes_against_dense(n, precision):
+    wl = cavity_chain(n)
+    psi = W.haar_psi(n, 3)
+    rho0 = np.outer(psi, psi.conj())
+    print(f"series N={n} {precision}", flush=True)
+    check(run(wl, precision, 1, (2, 1), rho0), run(wl, precision, 0, (2, 1), rho0), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64", "bf16x3"])
+@pytest.mark.parametrize("n,degree,isolated", [(130, 3, 0), (300, 9, 70), (700, 14, 1)])
+def test_general_models_against_oracle(n, degree, isolated, precision):
+    """Rows of H of very different length (a state coupled to twenty others,
+    states coupled to none), two components of H with different shifts, a
+    decoherence operator inside the basis."""
+    wl = random_model(n, degree, n, isolated=isolated)
+    psi = W.haar_psi(n, 5)
+    rho0 = np.outer(psi, psi.conj())
+    s = ev.GeneralSystem(wl)
+    ref, sink = ev.evolve(s, rho0, 20, sink0=0.125)
+    print(f"series general N={n} {precision}", flush=True)
+    got = run(wl, precision, 1, (20,), rho0)
+    check(got, (ref, sink), precision)
+
+
+def test_products_knob():
+    """The series is the default where H is sparse enough, asking for split
+    products or form 0 selects the dense ones, small systems have none."""
+    sol = P.Solver(W.photon_lattice(16, 16, gamma=0.05), "fp32")
+    psi = W.haar_psi(sol.n, 7)
+    rho0 = np.outer(psi, psi.conj())
+
+    def state():
+        sol.set_rho(rho0)
+        sol.step(5)
+        return sol.get_rho()[0]
+
+    default = state()
+    sol.set_products(1)
+    series = state()
+    sol.set_products(0)
+    dense = state()
+    sol.set_products(-1)
+    sol.set_split(True)
+    split = state()
+    sol.set_split(False)
+    again = state()
+    assert np.array_equal(default, series) and np.array_equal(again, series)
+    assert np.array_equal(dense, split) and not np.array_equal(dense, series)
+    for form in (-2, 2):
+        with pytest.raises(L.QmeError) as e:
+            sol.set_products(form)
+        assert e.value.status == L.QME_E_ARG
+    sol.close()
+    small = P.Solver(W.jc_single(), "fp32")
+    with pytest.raises(L.QmeError) as e:
+        small.set_products(1)
+    assert e.value.status == L.QME_E_UNSUPPORTED
+    small.close()
+
+
+@pytest.mark.parametrize("sizes", [(40, 200), (40, 600), (200, 1100), (40, 2100)])
+def test_batch_of_both_forms_equals_solo(sizes):
+    """Batches of series instances in every shape of their passes, beside
+    instances with dense products: each bitwise as alone."""
+    wls = [cavity_chain(n, dt=0.1 + 0.05 * k) for n in sizes for k in range(2)]
+    sols = []
+    for k, wl in enumerate(wls):
+        sol = P.Solver(wl, "fp32")
+        sol.set_products(1 if k % 4 != 1 else 0)
+        psi = W.haar_psi(sol.n, k)
+        sol.set_rho(np.outer(psi, psi.conj()))
+        sols.append(sol)
+    b = P.Batch(sols)
+    print(f"batch of both forms, N = {sizes}", flush=True)
+    b.step(3)
+    b.step(4)
+    torch.cuda.synchronize()
+    for k, (wl, sol) in enumerate(zip(wls, sols)):
+        alone = P.Solver(wl, "fp32")
+        alone.set_products(1 if k % 4 != 1 else 0)
+        alone.set_fold(False)
+        if k % 4 == 1:
+            alone.set_split(False)
+        psi = W.haar_psi(alone.n, k)
+        alone.set_rho(np.outer(psi, psi.conj()))
+        alone.step(7)
+        assert np.array_equal(sol.get_rho()[0], alone.get_rho()[0]), (sizes, k)
+        alone.close()
+    b.close()
+    for sol in sols:
+        sol.close()
