@@ -121,6 +121,19 @@ __global__ __launch_bounds__(kThreads, (BM == 32 && !(OPS & kBRow)) ? 5 : 1) voi
                                  w.slot < 0 ? nullptr : p.part + size_t(w.slot) * 2 * BM * BM);
 }
 
+// The tiles of a product that a caller lists.  Consecutive tiles of the list
+// (which share rows of the operands) go to one XCD.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void cgemm_listed_kernel(CgemmArgs<T> p, const int32_t *tiles,
+                                                                int count) {
+  __shared__ __align__(16) T smem[cgemm_s_smem<T, 32, kConjB>()];
+  const int per = (count + 7) >> 3;
+  const int t = (int(blockIdx.x) & 7) * per + (int(blockIdx.x) >> 3);
+  if (t >= count) return;
+  const int32_t at = tiles[t];
+  cgemm_s_tile<T, 32, kConjB>(p, at >> 16, at & 65535, smem);
+}
+
 // C = alpha * sum_s part[tile, s] + beta * X over the split tiles: one
 // 64-thread block per (split tile, 64 * V elements).  The chunks are loaded
 // in groups of 16 (one group for the split counts the planner makes) and X
@@ -272,6 +285,15 @@ static hipError_t split_reduce_tile(const CgemmArgs<T> &a, int tile, dim3 grid, 
   if (tile == 32) return launch_kernel(split_reduce_kernel<T, 32, LOWER>, grid, block, 0, s, a);
   return hipErrorInvalidValue;
 }
+
+template <typename T>
+hipError_t launch_cgemm_listed(const CgemmArgs<T> &a, const int32_t *tiles, int count, hipStream_t s) {
+  if (a.ld % 32 != 0 || a.ld / 32 > 32767 || count < 1) return hipErrorInvalidValue;
+  return launch_kernel(cgemm_listed_kernel<T>, dim3(unsigned((count + 7) / 8 * 8)), dim3(kThreads), 0,
+                       s, a, tiles, count);
+}
+template hipError_t launch_cgemm_listed<float>(const CgemmArgs<float> &, const int32_t *, int, hipStream_t);
+template hipError_t launch_cgemm_listed<double>(const CgemmArgs<double> &, const int32_t *, int, hipStream_t);
 
 template <typename T>
 hipError_t launch_split_reduce(const CgemmArgs<T> &a, int tile, bool lower, hipStream_t s) {

@@ -97,6 +97,7 @@ struct qme_ctx {
   double *h_val = nullptr;
   int32_t *t_row = nullptr, *t_col = nullptr;
   double *t_val = nullptr;
+  std::vector<int32_t> adj_tiles;     // host: frechet_tiles, made by the first series adjoint
   std::vector<int64_t> term_offset;   // host: entries of term p are [off[p], off[p+1])
   int squarings = 0;                  // of the propagator build
   // failure injection for recovery tests: when QME_FAULT_AT_STEP=k is set in

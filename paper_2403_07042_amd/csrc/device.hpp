@@ -151,6 +151,10 @@ hipError_t launch_cgemm_f32(const CgemmArgs<float> &a, int tile, const GemmOps &
                             hipStream_t s);
 hipError_t launch_cgemm_f64(const CgemmArgs<double> &a, int tile, const GemmOps &o,
                             hipStream_t s);
+// C += A M^H on the 32 x 32 tiles listed in `tiles` (device: row * 65536 +
+// column, in tiles) only.
+template <typename T>
+hipError_t launch_cgemm_listed(const CgemmArgs<T> &a, const int32_t *tiles, int count, hipStream_t s);
 // Split-BF16x3 products on FP32 planes (tile 64, NT forms only).
 hipError_t launch_cgemm_bf16x3(const CgemmArgs<float> &a, const GemmOps &o, hipStream_t s);
 // The six bf16 planes of a complex FP32 matrix (elems per plane), with the
@@ -375,13 +379,14 @@ hipError_t launch_set_diag(T *x_re, T *x_im, int64_t ld, int64_t n, const double
 
 // One row pass of the rotation by the propagator's series (series_tile.hpp):
 // each row x of X becomes conj(U) x (sign = 1) or U x (sign = -1).
-enum { kSeriesFirst = 0, kSeriesLower = 1, kSeriesFold = 2 };
+enum { kSeriesFirst = 0, kSeriesLower = 1, kSeriesFold = 2, kSeriesBoth = 3 };
 constexpr int kSeriesMaxOrder = 24;   // as kMaxSeriesOrder of the plan
 constexpr int64_t kSeriesMaxN = 8192;   // the rows of a workgroup fit its LDS
 template <typename T>
 struct SeriesArgs {
   const T *x_re, *x_im;      // ld x ld, rows and columns < n read
   T *o_re, *o_im;
+  T *r_re, *r_im;            // kSeriesBoth: the result's rows
   int64_t ld, n;
   // K dt (K = H less the shift): slot s holds state slot_col[s]; the entries
   // of the 64 slots of slice q are those at [e * 64 + lane], slice_off[q] <= e

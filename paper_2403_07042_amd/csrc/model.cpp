@@ -911,6 +911,38 @@ SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
   return p;
 }
 
+std::vector<int32_t> frechet_tiles(const Csr &h, double dt, double tol) {
+  const int64_t n = h.n, t = (n + 31) / 32;
+  double theta = 0.0;
+  std::vector<std::vector<char>> near(static_cast<size_t>(t), std::vector<char>(size_t(t), 0));
+  for (int64_t i = 0; i < n; ++i) {
+    double sum = 0.0;
+    near[size_t(i / 32)][size_t(i / 32)] = 1;
+    for (int64_t e = h.ptr[i]; e < h.ptr[i + 1]; ++e) {
+      near[size_t(i / 32)][size_t(h.col[e] / 32)] = 1;
+      if (h.col[e] != i) sum += std::fabs(h.val[e]) * dt;
+    }
+    theta = std::max(theta, sum);
+  }
+  int hops = 1;
+  for (double term = theta; term > tol && hops < t; term *= theta / double(hops)) ++hops;
+  std::vector<std::vector<char>> reach = near;
+  for (int k = 1; k < hops; ++k) {
+    std::vector<std::vector<char>> next = reach;
+    for (size_t a = 0; a < size_t(t); ++a)
+      for (size_t b = 0; b < size_t(t); ++b)
+        if (reach[a][b])
+          for (size_t c = 0; c < size_t(t); ++c) next[a][c] |= near[b][c];
+    if (next == reach) break;
+    reach.swap(next);
+  }
+  std::vector<int32_t> out;
+  for (size_t a = 0; a < size_t(t); ++a)
+    for (size_t b = 0; b < size_t(t); ++b)
+      if (reach[a][b]) out.push_back(int32_t(a * 65536 + b));
+  return out;
+}
+
 // ------------------------------------------------------------ Frechet
 
 // y = (-i tau H) x for complex planar dense x (rows), H sparse real symmetric.

@@ -182,6 +182,12 @@ constexpr int kMaxSeriesOrder = 24;
 std::vector<double> series_coefficients(double theta, double tol);
 SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave);
 
+// The 32 x 32 tiles (row * 65536 + column, rows in order) of G that reach the
+// gradient's entries W[c][r], (r, c) in H's pattern, of W = L(-i H dt, G): those
+// holding an entry (a, b) of states at most l couplings apart, l the first with
+// (|H_offdiag| dt)^l / l! below tol: an entry one further reaches W with less.
+std::vector<int32_t> frechet_tiles(const Csr &h, double dt, double tol);
+
 // W = L(A, G), the Frechet derivative of exp at A = -i H dt applied to G
 // in its adjoint form tr(G L(A, E)) = tr(L(A, G) E); G and W are complex
 // planar n x n (FP64, row-major).

@@ -103,6 +103,7 @@ hipError_t launch_mode(const SeriesArgs<T> &a, int mode, hipStream_t s) {
     case kSeriesFirst: return launch_one<T, R, S, NT, kSeriesFirst>(a, s);
     case kSeriesLower: return launch_one<T, R, S, NT, kSeriesLower>(a, s);
     case kSeriesFold: return launch_one<T, R, S, NT, kSeriesFold>(a, s);
+    case kSeriesBoth: return launch_one<T, R, S, NT, kSeriesBoth>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

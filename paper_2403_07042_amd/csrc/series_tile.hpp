@@ -61,6 +61,7 @@ __device__ __forceinline__ int64_t series_unit(int c, int g, int groups) {
 }
 
 // MODE kSeriesFirst: reads the state, writes W^dag in blocks (series_unit).
+// MODE kSeriesBoth: as kSeriesFirst, and writes W's own rows too.
 // MODE kSeriesLower: reads those blocks, writes the rows of rho_u on and below
 // the diagonal.
 // MODE kSeriesFold: as kSeriesLower with the previous step's factor and the
@@ -78,6 +79,8 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   // arithmetic must not depend on what the compiler fuses in each shape)
 #pragma clang fp contract(off)
   typedef T unit __attribute__((ext_vector_type(R)));
+  constexpr bool kBlocks = MODE == kSeriesFirst || MODE == kSeriesBoth;   // reads rows, writes blocks
+  constexpr bool kRows = MODE != kSeriesFirst;                            // writes rows
   // v in LDS: a unit's 16-byte parts (one or two) in planes of their own, so
   // that lanes with neighbouring slots read without bank conflicts; the
   // imaginary planes follow the real ones
@@ -143,7 +146,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   unsigned col[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) col[s] = unsigned(a.slot_col[unsigned(min((wave * S + s) * 64 + lane, n - 1))]);
-  if constexpr (MODE == kSeriesFirst) {
+  if constexpr (kBlocks) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const T *p_re = a.x_re + int64_t(row[r]) * a.ld, *p_im = a.x_im + int64_t(row[r]) * a.ld;
@@ -238,7 +241,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
 
   // (the row passes hand their results to LDS, by state, so that the rows are
   // written in order: the slots' order would leave parts of lines)
-  if constexpr (MODE != kSeriesFirst) __syncthreads();
+  if constexpr (kRows) __syncthreads();
   const T w1 = sgn * T(a.ratio[1]);
   double eps = 0.0;                    // the previous step's factor less 1
   double row_d[R];
@@ -269,10 +272,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
         dr = series_fma<T>(-q_im, yi, series_fma<T>(q_re, yr, dr));
         di = series_fma<T>(q_im, yr, series_fma<T>(q_re, yi, di));
       }
-      if constexpr (MODE == kSeriesFirst) {
-        w_re[r] = xr + dr;
-        w_im[r] = -(xi + di);
-      } else if constexpr (MODE == kSeriesLower) {
+      if constexpr (MODE != kSeriesFold) {
         w_re[r] = xr + dr;
         w_im[r] = xi + di;
       } else {
@@ -286,16 +286,15 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
         w_im[r] = xi + series_fma<T>(f, xi + di, di);
       }
     }
-    if constexpr (MODE == kSeriesFirst) {
+    if constexpr (kBlocks) {
       const int64_t u = series_unit(0, group, groups);
       const unsigned o = unsigned(series_unit(slot, 0, groups));
       (reinterpret_cast<unit *>(a.o_re) + u)[o] = w_re;
-      (reinterpret_cast<unit *>(a.o_im) + u)[o] = w_im;
-    } else {
-      put(lds, int(c), w_re, w_im);
+      (reinterpret_cast<unit *>(a.o_im) + u)[o] = -w_im;
     }
+    if constexpr (kRows) put(lds, int(c), w_re, w_im);
   }
-  if constexpr (MODE != kSeriesFirst) {
+  if constexpr (kRows) {
     __syncthreads();
     unit w_re[S], w_im[S];
 #pragma unroll
@@ -314,8 +313,9 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       if (q0 + r >= n) break;
-      T *p_re = a.o_re + int64_t(row[r]) * a.ld, *p_im = a.o_im + int64_t(row[r]) * a.ld;
-      const int end = MODE == kSeriesFold ? n : row[r] + 1;
+      T *p_re = (kBlocks ? a.r_re : a.o_re) + int64_t(row[r]) * a.ld;
+      T *p_im = (kBlocks ? a.r_im : a.o_im) + int64_t(row[r]) * a.ld;
+      const int end = MODE == kSeriesLower ? row[r] + 1 : n;
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         const unsigned c = unsigned(s * NT + tid);

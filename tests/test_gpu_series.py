@@ -174,3 +174,28 @@ def test_batch_of_both_forms_equals_solo(sizes):
     b.close()
     for sol in sols:
         sol.close()
+
+
+@pytest.mark.parametrize("precision,tol", [("fp32", 1e-4), ("fp64", 1e-9)])
+@pytest.mark.parametrize("make", [lambda: W.photon_lattice(27, 21, gamma=0.05),      # N = 1134, ld = 1152
+                                  lambda: W.photon_lattice(9, 7, mu=0.1, g=0.1, dt=0.1, gamma=0.05),
+                                  W.tch_2x2, lambda: random_model(300, 5, 8, isolated=40)])
+def test_adjoint_against_dense(make, precision, tol):
+    """Gradients by the series (rotations by row passes, the sum of rho X on
+    the tiles that reach the gradient only) against the dense products',
+    recomputed and whole segments."""
+    wl = make()
+    sol = P.Solver(wl, precision)
+    psi = W.haar_psi(sol.n, 4)
+    sol.set_rho(np.outer(psi, psi.conj()))
+    obs = np.random.default_rng(6).uniform(0.0, 1.0, sol.n)
+    out = {}
+    for form in (0, 1):
+        sol.set_products(form)
+        print(f"adjoint N={sol.n} {precision} form={form}", flush=True)
+        out[form] = [sol.adjoint(7, obs, checkpoint_every=every) for every in (3, 16)]
+    sol.close()
+    for (f0, g0), (f1, g1) in zip(out[0], out[1]):
+        assert abs(f0 - f1) < tol * abs(f0)
+        assert np.linalg.norm(g0 - g1) < tol * np.linalg.norm(g0)
+    assert np.array_equal(out[1][0][1], out[1][1][1])
