@@ -849,7 +849,9 @@ SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
     for (const auto &e : row) sum += std::fabs(e.second);
     p.theta = std::max(p.theta, sum);
   }
-  p.coef = series_coefficients(p.theta, fp64 ? 1e-18 : 1e-12);
+  // FP32: a term that stays below 2e-11 (a 3000th of a state's rounding) is
+  // left out; FP64: as propagator_increment
+  p.coef = series_coefficients(p.theta, fp64 ? 1e-18 : 2e-11);
   p.order = int(p.coef.size()) - 1;
   size_t nnz = 0;
   for (const auto &row : rows) nnz += row.size();

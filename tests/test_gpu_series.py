@@ -199,3 +199,48 @@ def test_adjoint_against_dense(make, precision, tol):
         assert abs(f0 - f1) < tol * abs(f0)
         assert np.linalg.norm(g0 - g1) < tol * np.linalg.norm(g0)
     assert np.array_equal(out[1][0][1], out[1][1][1])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [33, 256, 257, 1025, 2049, 3073, 4097, 5121])
+def test_pure_against_dense(n, precision):
+    """Pure-state steps in one launch per call (a workgroup per vector)
+    against one launch per step over dU, at the edges of the shapes; the
+    vectors of a call and the split of a run into calls change no bit."""
+    wl = dict(cavity_chain(n), jumps=[])
+    sol = P.Solver(wl, precision)
+    psi = np.stack([W.haar_psi(n, 9), W.haar_psi(n, 10)])
+    out = {}
+    for form, calls in ((1, (9,)), ("split", (4, 1, 4)), (0, (9,))):
+        sol.set_products(0 if form == 0 else 1)
+        sol.set_psi(psi)
+        print(f"pure N={n} {precision} form={form}", flush=True)
+        for k in calls:
+            sol.step_pure(k)
+        out[form] = sol.get_psi()
+    sol.set_products(1)
+    sol.set_psi(psi[1])
+    sol.step_pure(9)
+    assert np.array_equal(sol.get_psi(), out[1][1])
+    sol.close()
+    assert np.array_equal(out["split"], out[1])
+    tol = 2 * {"fp32": 1e-5, "fp64": 1e-12}[precision]
+    assert np.abs(out[1] - out[0]).max() < tol * np.abs(out[0]).max()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n,degree", [(140, 3), (400, 14)])
+def test_pure_general_models_against_oracle(n, degree, precision):
+    """Rows of H longer than the entries kept in registers, and components
+    whose phases differ (a pure state keeps its phase)."""
+    wl = dict(random_model(n, degree, n), jumps=[])
+    psi = W.haar_psi(n, 5)
+    sol = P.Solver(wl, precision)
+    sol.set_products(1)
+    sol.set_psi(psi)
+    print(f"pure general N={n} {precision}", flush=True)
+    sol.step_pure(50)
+    got = sol.get_psi()
+    sol.close()
+    ref = ev.evolve_pure(ev.GeneralSystem(wl), psi, 50)
+    assert np.abs(got - ref).max() < {"fp32": 1e-5, "fp64": 1e-11}[precision] * np.abs(ref).max()
