@@ -506,7 +506,18 @@ static qme_status step_impl(qme_ctx *c, void *state, int64_t n_steps, void *ws,
     SmallArgs<T> a{re, re + pe, reinterpret_cast<double *>(re + 2 * pe),
                    static_cast<const T *>(c->du_re), static_cast<const T *>(c->du_im),
                    c->ld, int(c->n), c->model.dt, c->d, c->leak, c->pi, c->cg,
-                   c->jt.n_gather, n_steps, c->trw};
+                   c->jt.n_gather, n_steps, c->trw, c->du_row_max, {}};
+    static_assert(sizeof(a.series.ratio) == sizeof(c->series_ratio), "one length of series");
+    if (c->small_order > 0) {
+      a.series.order = c->small_order;
+      a.series.entries = c->small_entries;
+      a.series.slot_bytes = series_slot_bytes(c->n);
+      a.series.slot_col = c->s_col;
+      a.series.entry_at = c->s_at;
+      a.series.entry_val = static_cast<const T *>(c->s_val);
+      a.series.phase = c->s_phase;
+      std::copy(std::begin(c->series_ratio), std::end(c->series_ratio), a.series.ratio);
+    }
     hipError_t e = mark(c, s, -1);
     if (e == hipSuccess) e = launch_small_steps<T>(a, s);
     if (e == hipSuccess) e = mark(c, s, 0);
@@ -563,6 +574,15 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
     return QME_E_NUMERIC;
   }
   c->jt = jump_tables(c->model);
+  if (c->n <= kSmallN) {
+    c->du_row_max = 0;
+    for (int64_t i = 0; i < c->n; ++i) {
+      int entries = 0;
+      for (int64_t j = 0; j < c->n; ++j)
+        entries += c->du_re_host[size_t(i * c->n + j)] != 0.0 || c->du_im_host[size_t(i * c->n + j)] != 0.0;
+      c->du_row_max = std::max(c->du_row_max, entries);
+    }
+  }
 
   HIP_OK(hipGetDevice(&c->device));
   HIP_OK(hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device));
@@ -633,8 +653,15 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
       c->s_col = reinterpret_cast<int32_t *>(t + o_col);
       c->s_off = reinterpret_cast<int32_t *>(t + o_off);
       static_assert(kSeriesMaxOrder == kMaxSeriesOrder, "the plan's orders fit the passes");
-      c->series_order = sp.order;
-      c->series_faster = sp.faster;
+      // (systems of the single-workgroup path keep it: the row passes would be
+      // several launches per step)
+      if (n > kSmallN) {
+        c->series_order = sp.order;
+        c->series_faster = sp.faster;
+      } else {
+        c->small_order = sp.order;
+        c->small_entries = sp.slice_off[1];
+      }
       for (int k = 1; k <= sp.order; ++k) c->series_ratio[k] = sp.coef[size_t(k)] / sp.coef[size_t(k) - 1];
       c->series_phase = sp.has_phase;
     }

@@ -22,6 +22,7 @@ struct qme_ctx {
   int precision = QME_FP32;
   int64_t elem = 4;                   // storage bytes per real
   int64_t n = 0, ld = 0;
+  int du_row_max = qme::kSmallN;      // n <= kSmallN: the most entries in a row of dU
   int tile1 = 64, tile2 = 64;         // tiles of the two products of a step
   bool tail_split = true;             // qme_set_split
   bool split_asked = false;           // qme_set_split(ctx, 1) was called
@@ -45,6 +46,7 @@ struct qme_ctx {
   void *du_split = nullptr;                  // BF16X3: dU as six bf16 planes (split once)
   // the propagator as a series (plan_series); series_order 0: none
   int series_order = 0;
+  int small_order = 0, small_entries = 0;    // n <= kSmallN: SmallSeries
   bool series_faster = false;                // than the dense products (the default's choice)
   double series_ratio[qme::kSeriesMaxOrder + 1] = {};
   bool series_phase = false;                 // the components' shifts differ

@@ -235,6 +235,16 @@ hipError_t launch_diag(const T *x_re, int64_t ld, int64_t n, double *out, hipStr
 // launch (state and dU held in LDS; see small.hip).  re / im / aux: the
 // state buffer (planes of ld x ld, FP64 scalars), updated in place.
 constexpr int kSmallN = 32;
+// The propagator's series of such a system (one slice of slots, SeriesArgs);
+// order 0: none.
+template <typename T>
+struct SmallSeries {
+  int order = 0, entries = 0, slot_bytes = 16;
+  const int32_t *slot_col = nullptr, *entry_at = nullptr;
+  const T *entry_val = nullptr;
+  const double *phase = nullptr;
+  double ratio[25] = {};
+};
 template <typename T>
 struct SmallArgs {
   T *re, *im;
@@ -249,6 +259,8 @@ struct SmallArgs {
   int n_gather;
   int64_t steps;
   const double *trw;       // trace weights (see DissArgs)
+  int row_max = kSmallN;   // the most entries that a row of dU has
+  SmallSeries<T> series;
 };
 template <typename T>
 hipError_t launch_small_steps(const SmallArgs<T> &a, hipStream_t s);

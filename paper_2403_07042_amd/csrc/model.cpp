@@ -804,7 +804,6 @@ std::vector<double> series_coefficients(double theta, double tol) {
 SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
   SeriesPlan p;
   const int64_t n = h.n;
-  if (n <= 32) return p;   // the single-workgroup path's sizes
   // connected components of the couplings
   std::vector<int32_t> root(static_cast<size_t>(n));
   for (int64_t i = 0; i < n; ++i) root[size_t(i)] = int32_t(i);

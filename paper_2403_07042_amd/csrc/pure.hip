@@ -34,12 +34,12 @@
 #include <cstdint>
 #include <cstring>
 #include <string>
-#include <type_traits>
 #include <utility>
 #include <vector>
 
 #include "ctx.hpp"
 #include "device.hpp"
+#include "lane_sums.hpp"
 #include "model.hpp"
 #include "qme.h"
 
@@ -152,23 +152,6 @@ struct PureSeriesArgs {
   double ratio[kSeriesMaxOrder + 1];
   int64_t steps;
 };
-
-// Sum over the 16 lanes of a row, in every lane of it (rotations within the
-// row: no LDS access).
-__device__ __forceinline__ double row_sum(double x) {
-  auto turned = [](double v, auto by) {
-    const long long b = __builtin_bit_cast(long long, v);
-    constexpr int ctrl = 0x120 + decltype(by)::value;   // row_ror
-    const int lo = __builtin_amdgcn_update_dpp(0, int(b), ctrl, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), ctrl, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | unsigned(lo));
-  };
-  x += turned(x, std::integral_constant<int, 8>{});
-  x += turned(x, std::integral_constant<int, 4>{});
-  x += turned(x, std::integral_constant<int, 2>{});
-  x += turned(x, std::integral_constant<int, 1>{});
-  return x;
-}
 
 // Waves of S slices of 64 states, the first C entries of each slice in
 // registers (FP64 with many slices: the slots packed in pairs).  TWO: two

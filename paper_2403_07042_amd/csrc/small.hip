@@ -11,7 +11,18 @@
 // Products accumulate in the storage type with scalar FMAs (k ascending);
 // the decoherence arithmetic is operation-for-operation that of the tiled
 // decoherence pass, so only the products' rounding order differs from it.
+//
+// small_rows_kernel: where the rows of dU have few entries (up to eight: states
+// that H does not connect have none) and the channels are few.  One element per
+// thread; a thread keeps what it needs of dU's rows, the decoherence factors
+// and the gathers in registers for all steps, and every wave forms the trace
+// itself, so a step is three LDS round trips with a barrier each (none for n <=
+// 8: one wave).  What bounds it is the latency of that chain.  The general
+// kernel reads dU and the tables from LDS again in every step and divides
+// every element index by n: N = 8 Jaynes-Cummings 2.15 -> 0.44 us per step, N =
+// 32 (FP32, three channels) 20.4 -> 1.6.
 #include "device.hpp"
+#include "lane_sums.hpp"
 
 #include <algorithm>
 
@@ -176,12 +187,318 @@ __global__ __launch_bounds__(kSmallThreads) void small_steps_kernel(SmallArgs<T>
 }
 
 template <typename T>
+__device__ __forceinline__ T __attribute__((ext_vector_type(2))) small_pair(T re, T im) {
+  T v __attribute__((ext_vector_type(2)));
+  v[0] = re;
+  v[1] = im;
+  return v;
+}
+
+// What one element's thread keeps for its decoherence step and the trace.
+template <typename T, int G>
+struct SmallElement {
+  typedef T cplx __attribute__((ext_vector_type(2)));
+  double f, gw[G];            // decay factor; per channel its weight (0: none)
+  int ga[G];                  // and where its element lies, below the diagonal
+  unsigned flip = 0;          // bit g: that element is the conjugate's
+  int dw;
+  double trw, leak, one;      // of the state whose diagonal this lane adds to the trace
+
+  __device__ __forceinline__ void load(const SmallArgs<T> &p, int i, int j, int lane) {
+    const int n = p.n;
+    f = 1.0 - 0.5 * p.dt * (p.d[i] + p.d[j]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      ga[g] = 0;
+      gw[g] = 0.0;
+      if (g < p.n_gather) {
+        const int pu = p.pi[int64_t(g) * n + i], pv = p.pi[int64_t(g) * n + j];
+        if (pu >= 0 && pv >= 0) {
+          ga[g] = pu >= pv ? pu * kSmallLd + pv : pv * kSmallLd + pu;
+          flip |= pu >= pv ? 0u : 1u << g;
+          gw[g] = p.dt * p.cg[int64_t(g) * n + i] * p.cg[int64_t(g) * n + j];
+        }
+      }
+    }
+    const int w = n <= 16 ? lane & 15 : lane & 31;
+    dw = w < n ? w * (kSmallLd + 1) : 0;
+    trw = w < n ? p.trw[w] : 0.0;
+    leak = w < n ? p.leak[w] : 0.0;
+    one = w < n ? 1.0 : 0.0;
+  }
+  // Z + dt D(Z) of this element, z its own value, s_z the lower triangle
+  __device__ __forceinline__ void decohere(const cplx &z, const cplx *s_z, double &xr, double &xi) const {
+    xr = f * double(z[0]);
+    xi = f * double(z[1]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const cplx h = s_z[ga[g]];
+      xr += gw[g] * double(h[0]);
+      xi += gw[g] * ((flip >> g) & 1u ? -double(h[1]) : double(h[1]));
+    }
+  }
+};
+
+// The step's scalars, the same in every thread.
+struct SmallScalars {
+  double sink, rot, lost, steps, scale;
+  template <typename T, int G>
+  __device__ __forceinline__ void advance(const SmallArgs<T> &p, const SmallElement<T, G> &e,
+                                          double zd) {
+    auto total = [&](double x) {
+      x = row_sum(x);
+      return p.n <= 16 ? x : x + __shfl_xor(x, 16);
+    };
+    const double tr = total(e.trw * zd);
+    lost = total(e.leak * zd);
+    rot = total(e.one * zd);
+    sink = sink + p.dt * lost;
+    steps = steps + 1.0;
+    scale = (1.0 - sink) / tr;
+  }
+};
+
+// L: entries of a row of dU, G: gather channels, NT: threads (n * n at most).
+template <typename T, int L, int G, int NT>
+__global__ __launch_bounds__(NT) void small_rows_kernel(SmallArgs<T> p) {
+  typedef T cplx __attribute__((ext_vector_type(2)));
+  __shared__ cplx s_rho[kSmallN * kSmallLd], s_t[kSmallN * kSmallLd], s_z[kSmallN * kSmallLd];
+  __shared__ int32_t s_k[kSmallN][L];
+  __shared__ cplx s_u[kSmallN][L];
+  const int n = p.n, tid = int(threadIdx.x), lane = tid & 63;
+  const double dt = p.dt;
+  // rows of dU without their zeros, in increasing k
+  if (tid < n) {
+    int c = 0;
+    for (int k = 0; k < n; ++k) {
+      const T ur = p.u_re[tid * p.ld + k], ui = p.u_im[tid * p.ld + k];
+      if ((ur != T(0) || ui != T(0)) && c < L) {
+        s_k[tid][c] = k;
+        s_u[tid][c++] = small_pair<T>(ur, ui);
+      }
+    }
+    for (; c < L; ++c) {
+      s_k[tid][c] = 0;
+      s_u[tid][c] = small_pair<T>(0, 0);
+    }
+  }
+  const int i = tid / n, j = tid - i * n;
+  const bool in = i < n, low = in && j <= i;
+  const int e = in ? i * kSmallLd + j : 0, ei = in ? i : 0, ej = in ? j : 0;
+  if (in) s_rho[e] = small_pair<T>(p.re[i * p.ld + j], p.im[i * p.ld + j]);
+  __syncthreads();
+  // this element's row i of dU against row j of rho, row i of T against row j
+  // of dU
+  int at1[L], at2[L];
+  cplx u1[L], u2[L];
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    at1[l] = ej * kSmallLd + s_k[ei][l];
+    u1[l] = s_u[ei][l];
+    at2[l] = ei * kSmallLd + s_k[ej][l];
+    u2[l] = s_u[ej][l];
+  }
+  SmallElement<T, G> el;
+  el.load(p, ei, ej, lane);
+  SmallScalars sc{p.aux[0], p.aux[1], p.aux[2], p.aux[3], p.aux[4]};
+
+  cplx own = s_rho[e];
+  for (int64_t s = 0; s < p.steps; ++s) {
+    // T = rho + dU rho (rho Hermitian)
+    T cr = T(0), ci = T(0);
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      const cplx m = s_rho[at1[l]];
+      cr = fma(u1[l][0], m[0], cr);
+      cr = fma(u1[l][1], m[1], cr);
+      ci = fma(u1[l][1], m[0], ci);
+      ci = fma(-u1[l][0], m[1], ci);
+    }
+    const cplx t = small_pair<T>(cr + own[0], ci + own[1]);
+    if (in) s_t[e] = t;
+    __syncthreads();
+    // Z = T + T conj(dU), lower triangle
+    cr = ci = T(0);
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      const cplx a = s_t[at2[l]];
+      cr = fma(a[0], u2[l][0], cr);
+      cr = fma(a[1], u2[l][1], cr);
+      ci = fma(a[1], u2[l][0], ci);
+      ci = fma(-a[0], u2[l][1], ci);
+    }
+    const cplx z = small_pair<T>(cr + t[0], ci + t[1]);
+    if (low) s_z[e] = z;
+    __syncthreads();
+    // trace, lost probability and renormalisation, in every wave
+    const double zd = double(s_z[el.dw][0]);
+    double xr, xi;
+    el.decohere(z, s_z, xr, xi);
+    sc.advance(p, el, zd);
+    // rho' = scale * (Z + dt D(Z)) on and below the diagonal, mirrored
+    if (low) {
+      const T a = T(xr * sc.scale), b = i == j ? T(0) : T(xi * sc.scale);
+      s_rho[e] = small_pair<T>(a, b);
+      s_rho[j * kSmallLd + i] = small_pair<T>(a, i == j ? b : -b);
+    }
+    __syncthreads();
+    own = s_rho[e];
+  }
+  if (in) {
+    p.re[i * p.ld + j] = own[0];
+    p.im[i * p.ld + j] = own[1];
+  }
+  if (tid == 0) {
+    p.aux[0] = sc.sink;
+    p.aux[1] = sc.rot;
+    p.aux[2] = sc.lost;
+    p.aux[3] = sc.steps;
+    p.aux[4] = sc.scale;
+  }
+}
+
+// Longer rows of dU, from the series of its exponential (series_tile.hpp) over
+// H's few entries a row (D at most): both rotations in Horner form on one LDS
+// array, along the rows and then along the columns, one barrier a term (v
+// alternates between two arrays).
+template <typename T, int D, int G, int NT>
+__global__ __launch_bounds__(NT) void small_series_kernel(SmallArgs<T> p) {
+  typedef T cplx __attribute__((ext_vector_type(2)));
+  __shared__ cplx s_v[2][kSmallN * kSmallLd];
+  __shared__ int32_t s_state[64], s_slot[kSmallN];
+  const int n = p.n, tid = int(threadIdx.x), lane = tid & 63;
+  const SmallSeries<T> &q = p.series;
+  const int i = tid / n, j = tid - i * n;
+  const bool in = i < n, low = in && j <= i;
+  const int e = in ? i * kSmallLd + j : 0, ei = in ? i : 0, ej = in ? j : 0;
+  if (tid < n) {
+    s_state[tid] = q.slot_col[tid];
+    s_slot[q.slot_col[tid]] = tid;
+  }
+  cplx x = small_pair<T>(0, 0);
+  if (in) x = small_pair<T>(p.re[i * p.ld + j], p.im[i * p.ld + j]);
+  __syncthreads();
+  // K's rows j and i as neighbours along this element's row and column
+  int at1[D], at2[D];
+  T k1[D], k2[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const bool has = d < q.entries;
+    const int a = has ? d * 64 + s_slot[ej] : 0, b = has ? d * 64 + s_slot[ei] : 0;
+    at1[d] = ei * kSmallLd + s_state[q.entry_at[a] / q.slot_bytes];
+    at2[d] = s_state[q.entry_at[b] / q.slot_bytes] * kSmallLd + ej;
+    k1[d] = has ? q.entry_val[a] : T(0);
+    k2[d] = has ? q.entry_val[b] : T(0);
+  }
+  // the phase left over by the two shifts: e^{i (shift_j - shift_i) dt} - 1
+  const double aj = q.phase[2 * ej], bj = q.phase[2 * ej + 1], ai = q.phase[2 * ei],
+               bi = -q.phase[2 * ei + 1];
+  const double q_re = ai + aj + (ai * aj - bi * bj), q_im = bi + bj + (ai * bj + bi * aj);
+  SmallElement<T, G> el;
+  el.load(p, ei, ej, lane);
+  SmallScalars sc{p.aux[0], p.aux[1], p.aux[2], p.aux[3], p.aux[4]};
+
+  int flip = 0;
+  // v <- x + ... ; returns d with (e^{sgn i K dt} x) = x + d
+  auto rotate = [&](const cplx &own, const int (&at)[D], const T (&k)[D], T sgn) {
+    cplx t;
+    if (in) s_v[flip][e] = own;
+    for (int m = q.order; m >= 1; --m) {
+      __syncthreads();
+      const cplx *v = s_v[flip];
+      t = small_pair<T>(0, 0);
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const cplx g = v[at[d]];
+        t[0] = fma(k[d], g[0], t[0]);
+        t[1] = fma(k[d], g[1], t[1]);
+      }
+      const T w = sgn * T(q.ratio[m]);
+      flip ^= 1;
+      if (m == 1) return small_pair<T>(-w * t[1], w * t[0]);
+      if (in) s_v[flip][e] = small_pair<T>(fma(-w, t[1], own[0]), fma(w, t[0], own[1]));
+    }
+    return t;
+  };
+  for (int64_t s = 0; s < p.steps; ++s) {
+    // T = rho e^{i K dt} along the rows, Z = e^{-i K dt} T along the columns
+    const cplx d1 = rotate(x, at1, k1, T(1));
+    const cplx t = small_pair<T>(x[0] + d1[0], x[1] + d1[1]);
+    const cplx d2 = rotate(t, at2, k2, T(-1));
+    // z = (1 + q)(t + d2)
+    const double yr = double(t[0]) + double(d2[0]), yi = double(t[1]) + double(d2[1]);
+    const cplx z = small_pair<T>(T(double(t[0]) + (double(d2[0]) + (q_re * yr - q_im * yi))),
+                                 T(double(t[1]) + (double(d2[1]) + (q_re * yi + q_im * yr))));
+    // (the array that no wave reads any more)
+    cplx *s_z = s_v[flip];
+    if (low) s_z[e] = z;
+    __syncthreads();
+    const double zd = double(s_z[el.dw][0]);
+    double xr, xi;
+    el.decohere(z, s_z, xr, xi);
+    sc.advance(p, el, zd);
+    // rho' = scale * (Z + dt D(Z)) on and below the diagonal, mirrored
+    flip ^= 1;
+    cplx *s_x = s_v[flip];
+    if (low) {
+      const T a = T(xr * sc.scale), b = i == j ? T(0) : T(xi * sc.scale);
+      s_x[e] = small_pair<T>(a, b);
+      s_x[j * kSmallLd + i] = small_pair<T>(a, i == j ? b : -b);
+    }
+    __syncthreads();
+    x = s_x[e];
+    flip ^= 1;
+  }
+  if (in) {
+    p.re[i * p.ld + j] = x[0];
+    p.im[i * p.ld + j] = x[1];
+  }
+  if (tid == 0) {
+    p.aux[0] = sc.sink;
+    p.aux[1] = sc.rot;
+    p.aux[2] = sc.lost;
+    p.aux[3] = sc.steps;
+    p.aux[4] = sc.scale;
+  }
+}
+
+template <typename T, int NT>
+static hipError_t launch_small_series(const SmallArgs<T> &a, hipStream_t s) {
+  const dim3 one(1), threads(NT);
+  if (a.series.entries <= 4) return launch_kernel(small_series_kernel<T, 4, 6, NT>, one, threads, 0, s, a);
+  return launch_kernel(small_series_kernel<T, 8, 6, NT>, one, threads, 0, s, a);
+}
+
+template <typename T, int NT>
+static hipError_t launch_small_rows(const SmallArgs<T> &a, hipStream_t s) {
+  const dim3 one(1), threads(NT);
+  if (a.n_gather <= 2) {
+    if (a.row_max <= 2) return launch_kernel(small_rows_kernel<T, 2, 2, NT>, one, threads, 0, s, a);
+    if (a.row_max <= 4) return launch_kernel(small_rows_kernel<T, 4, 2, NT>, one, threads, 0, s, a);
+    return launch_kernel(small_rows_kernel<T, 8, 2, NT>, one, threads, 0, s, a);
+  }
+  if (a.row_max <= 4) return launch_kernel(small_rows_kernel<T, 4, 6, NT>, one, threads, 0, s, a);
+  return launch_kernel(small_rows_kernel<T, 8, 6, NT>, one, threads, 0, s, a);
+}
+
+template <typename T>
 hipError_t launch_small_steps(const SmallArgs<T> &a, hipStream_t s) {
   if (a.n < 1 || a.n > kSmallN || a.ld < a.n || a.steps < 0) return hipErrorInvalidValue;
   for (int64_t done = 0; done < a.steps; done += kSmallStepsPerLaunch) {
     SmallArgs<T> b = a;
     b.steps = std::min<int64_t>(kSmallStepsPerLaunch, a.steps - done);
-    hipError_t e = launch_kernel(small_steps_kernel<T>, dim3(1), dim3(kSmallThreads), 0, s, b);
+    // up to eight entries in a row of dU: two sweeps over them against two per
+    // term of the series (N = 32, three channels, FP64: 5.1 against 5.6 us per
+    // step); else the series while H's rows have up to eight (N = 32 lattice
+    // 17.0 -> 2.7 us FP32, 16.6 -> 4.8 FP64; N = 12 2.4 -> 1.2 and 2.0)
+    hipError_t e;
+    if (a.n_gather <= 6 && a.row_max <= 8)
+      e = a.n <= 8 ? launch_small_rows<T, 64>(b, s)
+          : a.n <= 16 ? launch_small_rows<T, 256>(b, s) : launch_small_rows<T, 1024>(b, s);
+    else if (a.n_gather <= 6 && a.series.order > 0 && a.series.entries <= 8)
+      e = a.n <= 16 ? launch_small_series<T, 256>(b, s) : launch_small_series<T, 1024>(b, s);
+    else
+      e = launch_kernel(small_steps_kernel<T>, dim3(1), dim3(kSmallThreads), 0, s, b);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -244,3 +244,42 @@ def test_pure_general_models_against_oracle(n, degree, precision):
     sol.close()
     ref = ev.evolve_pure(ev.GeneralSystem(wl), psi, 50)
     assert np.abs(got - ref).max() < {"fp32": 1e-5, "fp64": 1e-11}[precision] * np.abs(ref).max()
+
+
+def many_channels():
+    """Two cavities (one and two atoms, cap 1), every decay and dephasing: N = 32
+    with eight channels inside the basis."""
+    jumps = [(W.PHOTON_LEAK, c, -1, 0.02 + 0.01 * c) for c in range(2)]
+    for kind in (W.ATOM_DECAY, W.ATOM_DEPHASE):
+        jumps += [(kind, c, k, 0.01) for c, k in ((0, 0), (1, 0), (1, 1))]
+    return {"name": "channels", "atoms": [1, 2], "photon_cap": [1, 1], "exc_min": 0, "exc_max": -1,
+            "omega_c": [1.0, 1.05], "omega_a": [0.9, 1.0, 1.1], "g": [0.1, 0.08, 0.12],
+            "hops": [(0, 1, 0.05)], "jumps": jumps, "dt": 0.05}
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("make", [
+    W.jc_single, lambda: W.jc_single(cap=6),                       # N = 8, 14: two entries a row of dU
+    lambda: W.jc_single(cap=15),                                   # N = 32
+    lambda: W.photon_lattice(4, 3, mu=0.1, gamma=0.05, dt=0.1, atoms_per_site=0, g=0.0),   # N = 12: series
+    lambda: W.photon_lattice(17, 1, mu=0.1, gamma=0.05, dt=0.1, atoms_per_site=0, g=0.0),
+    lambda: W.photon_lattice(4, 4, mu=0.1, g=0.1, gamma=0.05, dt=0.1),                     # N = 32
+    many_channels,                                                 # the general kernel
+    lambda: dict(random_model(24, 4, 2)),                          # a row of H past eight entries
+])
+def test_single_workgroup_kernels_against_oracle(make, precision):
+    wl = make()
+    general = wl.get("general", False)
+    s = ev.GeneralSystem(wl) if general else ev.System(wl)
+    psi = W.haar_psi(s.n, 13)
+    rho0 = np.outer(psi, psi.conj())
+    ref, sink = ev.evolve(s, rho0, 60, sink0=0.125)
+    sol = P.Solver(wl, precision)
+    sol.set_rho(rho0, sink=0.125)
+    print(f"single workgroup N={s.n} {precision}", flush=True)
+    sol.step(41)
+    sol.step(19)
+    rho, got_sink = sol.get_rho()
+    _, trace, _ = sol.observe()
+    sol.close()
+    check((rho, got_sink, trace), (ref, sink), precision)
