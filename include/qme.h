@@ -175,7 +175,7 @@ qme_status qme_state_layout(const qme_ctx *ctx, int64_t *n, int64_t *ld,
                             int64_t *elem_bytes, size_t *state_bytes);
 
 /* Device workspace qme_step needs (caller-allocated, 256-byte aligned):
- * four product planes of ld x ld elements, N FP64 values (the diagonal kept
+ * four product planes of ld x ld elements, 2 N FP64 values (the diagonals kept
  * by folded steps, qme_set_fold) and, for contexts whose
  * products are too small to occupy the device, the partial slots of their
  * k-split (qme_set_split; at most 12 planes, sized for every tile edge
@@ -560,7 +560,11 @@ qme_status qme_set_fused(qme_ctx *ctx, int32_t enable);
  * is the renormalisation "folded into the next product" and saves the
  * decoherence pass.  Applies to FP32 contexts whose lower-product tile is 64
  * or 32, and to FP64 and BF16X3 contexts; results differ from the unfolded
- * step by rounding only.  enable: 0 or 1, else QME_E_ARG. */
+ * step by rounding only.  Steps by the series (qme_set_products) fold in every
+ * precision: one pass per step rotates each row, applies the factor and starts
+ * the next step's rotation, and the renormalisation factor stays pending until
+ * the call's closing pass.  (A profiled call, qme_profile_enable, runs a step's
+ * two passes: the same arithmetic.)  enable: 0 or 1, else QME_E_ARG. */
 qme_status qme_set_fold(qme_ctx *ctx, int32_t enable);
 
 /* Tile body of the FP32 products whose second operand is read by rows (all

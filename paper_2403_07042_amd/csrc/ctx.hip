@@ -325,13 +325,13 @@ bool uses_fold(const qme_ctx *c) {
 
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// The step workspace: 4 product planes, the diagonal of Z (N FP64), the
+// The step workspace: 4 product planes, the diagonals of Z (2 N FP64), the
 // partial slots of small-launch splits.
 template <typename T>
 static T *split_area_of(const qme_ctx *c, void *ws) {
   if (c->split_elems == 0) return nullptr;
   return reinterpret_cast<T *>(static_cast<char *>(ws) + align256(4 * plane_elems(c) * sizeof(T)) +
-                               align256(sizeof(double) * size_t(c->n)));
+                               align256(2 * sizeof(double) * size_t(c->n)));
 }
 
 // Whether a folded step's trace is formed by the next step's first product:
@@ -359,49 +359,75 @@ static bool trace_in_first_product(const qme_ctx *c, T *area) {
   return false;
 }
 
-// Folded steps by the series: the second pass writes the decoherence step of
-// its rows (unscaled) into the state; the factor of step k is applied by the
-// second pass of step k + 1, so that the trace it comes from can be formed
-// beside the first one.  Under profiling the trace keeps the launches that
-// the dense step would give it (the same sums, bitwise), so that the launch
-// counts per kind mean the same for both forms.
+// Folded steps by the series: the first step's first pass, one pass per further
+// step (kSeriesStep: the rows go through a step's second and the next one's
+// first rotation without leaving the compute unit; W^dag alternates between
+// the workspace's plane pairs), the last second pass into the state.  Step k's
+// trace is formed beside the pass after the one that leaves its diagonal, and
+// its factor stays pending: the closing pass applies the last one.  Under
+// profiling every step runs its two passes (the same arithmetic, bitwise), and
+// the trace keeps the launches that the dense step would give it, so that the
+// launch counts per kind mean the same for both forms.
 template <typename T>
 static hipError_t series_fold_steps(qme_ctx *c, void *state, int64_t n_steps, void *ws,
                                     hipStream_t s) {
+  if (n_steps == 0) return hipSuccess;
   const size_t pe = plane_elems(c);
   T *x_re = static_cast<T *>(state), *x_im = x_re + pe;
   double *aux = reinterpret_cast<double *>(x_im + pe);
-  T *y_re = static_cast<T *>(ws), *y_im = y_re + pe;
+  T *y = static_cast<T *>(ws);
   double *zdiag = reinterpret_cast<double *>(static_cast<char *>(ws) +
                                              align256(4 * pe * sizeof(T)));
-  const bool beside = !c->profiling || trace_in_first_product<T>(c, split_area_of<T>(c, ws));
-  const DissArgs<T> da{nullptr, nullptr, x_re, x_im, c->ld, c->n, c->model.dt, c->d, c->leak,
-                       c->pi, c->cg, 0, aux, aux, c->trw, zdiag};
-  for (int64_t k = 0; k < n_steps; ++k) {
-    SeriesArgs<T> first = series_args<T>(c, x_re, x_im, y_re, y_im, 1, false);
-    if (k > 0 && beside) {
-      first.tr_zdiag = zdiag;
-      first.tr_w = c->trw;
-      first.tr_leak = c->leak;
-      first.tr_aux = aux;
-      first.tr_dt = c->model.dt;
+  auto diag_of = [&](int64_t k) { return zdiag + (k & 1) * c->n; };
+  auto pend_of = [&](int64_t k) { return k > 0 ? aux + 4 : nullptr; };
+  auto pass = [&](const T *in, T *out, int64_t folds, int64_t traces) {
+    SeriesArgs<T> a = series_args<T>(c, in, in + pe, out, out + pe, 1, false);
+    if (folds >= 0) {
+      a.fold_d = c->d;
+      a.fold_dt = c->model.dt;
+      a.zdiag = diag_of(folds);
     }
-    SeriesArgs<T> second = series_args<T>(c, y_re, y_im, x_re, x_im, 1, false);
-    if (k > 0) second.scale = aux + 4;
-    second.fold_d = c->d;
-    second.fold_dt = c->model.dt;
-    second.zdiag = zdiag;
-    hipError_t e = mark(c, s, -1);
-    if (e == hipSuccess) e = launch_series_pass<T>(first, kSeriesFirst, s);
-    if (e == hipSuccess) e = mark(c, s, 0);
-    if (e == hipSuccess) e = launch_series_pass<T>(second, kSeriesFold, s);
-    if (e == hipSuccess) e = mark(c, s, 1);
-    if (e == hipSuccess && (!beside || k == n_steps - 1)) e = launch_trace<T>(da, s);
-    if (e == hipSuccess) e = mark(c, s, 2);
-    if (e != hipSuccess) return e;
+    if (traces >= 0) {
+      a.tr_zdiag = diag_of(traces);
+      a.tr_pend = pend_of(traces);
+      a.tr_w = c->trw;
+      a.tr_leak = c->leak;
+      a.tr_aux = aux;
+      a.tr_dt = c->model.dt;
+    }
+    return a;
+  };
+  auto trace = [&](int64_t k) {
+    DissArgs<T> da{nullptr, nullptr, x_re, x_im, c->ld, c->n, c->model.dt, c->d, c->leak,
+                   c->pi, c->cg, 0, aux, aux, c->trw, diag_of(k)};
+    da.pend = pend_of(k);
+    return launch_trace<T>(da, s);
+  };
+  hipError_t e = hipSuccess;
+  if (c->profiling) {
+    const bool beside = trace_in_first_product<T>(c, split_area_of<T>(c, ws));
+    for (int64_t k = 0; k < n_steps && e == hipSuccess; ++k) {
+      e = mark(c, s, -1);
+      if (e == hipSuccess)
+        e = launch_series_pass<T>(pass(x_re, y, -1, beside ? k - 1 : -1), kSeriesFirst, s);
+      if (e == hipSuccess) e = mark(c, s, 0);
+      if (e == hipSuccess) e = launch_series_pass<T>(pass(y, x_re, k, -1), kSeriesFold, s);
+      if (e == hipSuccess) e = mark(c, s, 1);
+      if (e == hipSuccess && (!beside || k == n_steps - 1)) e = trace(k);
+      if (e == hipSuccess) e = mark(c, s, 2);
+    }
+    launch_timer() = nullptr;   // the closing pass is no step's kernel
+  } else {
+    e = launch_series_pass<T>(pass(x_re, y, -1, -1), kSeriesFirst, s);
+    for (int64_t k = 0; k + 1 < n_steps && e == hipSuccess; ++k)
+      e = launch_series_pass<T>(pass(y + (k & 1) * 2 * pe, y + (1 - (k & 1)) * 2 * pe, k, k - 1),
+                                kSeriesStep, s);
+    const int64_t k = n_steps - 1;
+    if (e == hipSuccess)
+      e = launch_series_pass<T>(pass(y + (k & 1) * 2 * pe, x_re, k, k - 1), kSeriesFold, s);
+    if (e == hipSuccess) e = trace(k);
   }
-  launch_timer() = nullptr;   // the closing pass is no step's kernel
-  return n_steps > 0 ? launch_series_close<T>(x_re, x_im, c->ld, c->n, aux + 4, s) : hipSuccess;
+  return e == hipSuccess ? launch_series_close<T>(x_re, x_im, c->ld, c->n, aux + 4, s) : e;
 }
 
 // Folded steps: the lower-triangle product writes the decoherence step of
@@ -493,7 +519,7 @@ static qme_status step_impl(qme_ctx *c, void *state, int64_t n_steps, void *ws,
   const size_t pe = plane_elems(c);
   if (!uses_small_path(c) && uses_fold(c)) {
     hipError_t e = uses_series(c) ? series_fold_steps<T>(c, state, n_steps, ws, s)
-                                  : fold_steps<T>(c, state, n_steps, ws, s);
+                                   : fold_steps<T>(c, state, n_steps, ws, s);
     if (e != hipSuccess) {
       set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
       return QME_E_DEVICE;
@@ -1124,9 +1150,9 @@ extern "C" qme_status qme_state_layout(const qme_ctx *c, int64_t *n, int64_t *ld
 extern "C" qme_status qme_workspace_size(const qme_ctx *c, size_t *bytes) {
   set_error("");
   if (!c || !bytes) { set_error("NULL argument"); return QME_E_ARG; }
-  // the step's product planes, the diagonal of Z for folded steps and the
+  // the step's product planes, the diagonals of Z for folded steps and the
   // partial slots of products split along k
-  *bytes = align256(4 * plane_elems(c) * c->elem) + align256(sizeof(double) * size_t(c->n)) +
+  *bytes = align256(4 * plane_elems(c) * c->elem) + align256(2 * sizeof(double) * size_t(c->n)) +
            align256(c->split_elems * c->elem);
   return QME_OK;
 }

@@ -212,6 +212,8 @@ struct DissArgs {
   // systems, launch_dissipate with fuse_trace) the state is updated in place
   // by many blocks at once, so the two pairs differ and alternate by step.
   int slot_in = 0, slot_out = 0;
+  // when set, the diagonal is that of a state still to be multiplied by *pend
+  const double *pend = nullptr;
   int fuse_trace = 0;
   // bit j: gather channel j maps every state to itself or out of the basis
   // (dephasing), so its term reads the element itself and needs no load
@@ -391,7 +393,13 @@ hipError_t launch_set_diag(T *x_re, T *x_im, int64_t ld, int64_t n, const double
 
 // One row pass of the rotation by the propagator's series (series_tile.hpp):
 // each row x of X becomes conj(U) x (sign = 1) or U x (sign = -1).
-enum { kSeriesFirst = 0, kSeriesLower = 1, kSeriesFold = 2, kSeriesBoth = 3 };
+enum {
+  kSeriesFirst = 0,
+  kSeriesLower = 1,
+  kSeriesFold = 2,
+  kSeriesBoth = 3,
+  kSeriesStep = 4
+};
 constexpr int kSeriesMaxOrder = 24;   // as kMaxSeriesOrder of the plan
 constexpr int64_t kSeriesMaxN = 8192;   // the rows of a workgroup fit its LDS
 template <typename T>
@@ -410,13 +418,12 @@ struct SeriesArgs {
   double ratio[kSeriesMaxOrder + 1];   // [1 .. order]: the series' coefficient ratios
   const double *phase;       // e^{i shift dt} - 1 per state (re, im); nullptr: 0
   int32_t groups = 0;        // row groups (set by the launcher)
-  // kSeriesFirst: the previous step's trace formed beside the pass (as
-  // CgemmArgs::tr_*, scalar slots 0)
-  const double *tr_zdiag = nullptr, *tr_w = nullptr, *tr_leak = nullptr;
+  // a previous step's trace formed beside the pass (as CgemmArgs::tr_*, scalar
+  // slots 0), its diagonal still to be multiplied by *tr_pend (nullptr: 1)
+  const double *tr_zdiag = nullptr, *tr_w = nullptr, *tr_leak = nullptr, *tr_pend = nullptr;
   double *tr_aux = nullptr;
   double tr_dt = 0.0;
-  const double *scale = nullptr;   // kSeriesFold: the previous step's factor (nullptr: 1)
-  // kSeriesFold (as CgemmArgs::fold_*)
+  // kSeriesFold, kSeriesStep (as CgemmArgs::fold_*)
   const double *fold_d = nullptr;
   double fold_dt = 0.0;
   double *zdiag = nullptr;

@@ -122,6 +122,10 @@ __device__ __forceinline__ double trace_body(const DissArgs<T> &p, double *s_tr,
       l += s_lost[w];
       r += s_rot[w];
     }
+    if (p.pend) {
+      l *= *p.pend;
+      r *= *p.pend;
+    }
     const double sink = p.aux_in[sink_slot(p.slot_in)] + p.dt * l;
     const double steps = p.aux_in[steps_slot(p.slot_in)] + 1.0;
     const double scale = (1.0 - sink) / t;

@@ -8,26 +8,24 @@ namespace qme {
 // as the trace pass, so that the factor is bitwise the same
 static constexpr int kSeriesTraceThreads = 256;
 
-// The first pass of a folded step also forms the previous step's trace, in one
-// further workgroup that runs beside the others (tr_zdiag); the factor it
-// stores is applied by the step's second pass, which the stream orders after.
+// A pass may also form an earlier step's trace, in one further workgroup that
+// runs beside the others (tr_zdiag).
 template <typename T, int R, int S, int NT, int MODE>
 __global__ __launch_bounds__(NT, 4) void series_pass_kernel(SeriesArgs<T> a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  if constexpr (MODE == kSeriesFirst) {
-    if (a.tr_zdiag && blockIdx.x == gridDim.x - 1) {
-      DissArgs<T> d{};
-      d.n = a.n;
-      d.dt = a.tr_dt;
-      d.trw = a.tr_w;
-      d.leak = a.tr_leak;
-      d.zdiag = a.tr_zdiag;
-      d.aux_in = d.aux_out = a.tr_aux;
-      double *st = reinterpret_cast<double *>(lds);
-      constexpr int W = kSeriesTraceThreads / 64;
-      trace_body<T, kSeriesTraceThreads, true>(d, st, st + W, st + 2 * W);
-      return;
-    }
+  if (a.tr_zdiag && blockIdx.x == gridDim.x - 1) {
+    DissArgs<T> d{};
+    d.n = a.n;
+    d.dt = a.tr_dt;
+    d.trw = a.tr_w;
+    d.leak = a.tr_leak;
+    d.zdiag = a.tr_zdiag;
+    d.aux_in = d.aux_out = a.tr_aux;
+    d.pend = a.tr_pend;
+    double *st = reinterpret_cast<double *>(lds);
+    constexpr int W = kSeriesTraceThreads / 64;
+    trace_body<T, kSeriesTraceThreads, true>(d, st, st + W, st + 2 * W);
+    return;
   }
   const int group = series_group(int(blockIdx.x), a.groups);
   if (group >= a.groups) return;
@@ -93,7 +91,7 @@ hipError_t launch_one(const SeriesArgs<T> &in, hipStream_t s) {
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
   }
-  const unsigned grid = unsigned((a.groups + 7) / 8 * 8) + (MODE == kSeriesFirst && a.tr_zdiag ? 1 : 0);
+  const unsigned grid = unsigned((a.groups + 7) / 8 * 8) + (a.tr_zdiag ? 1 : 0);
   return launch_kernel(kernel, dim3(grid), dim3(NT), uint32_t(lds), s, a);
 }
 
@@ -103,6 +101,7 @@ hipError_t launch_mode(const SeriesArgs<T> &a, int mode, hipStream_t s) {
     case kSeriesFirst: return launch_one<T, R, S, NT, kSeriesFirst>(a, s);
     case kSeriesLower: return launch_one<T, R, S, NT, kSeriesLower>(a, s);
     case kSeriesFold: return launch_one<T, R, S, NT, kSeriesFold>(a, s);
+    case kSeriesStep: return launch_one<T, R, S, NT, kSeriesStep>(a, s);
     case kSeriesBoth: return launch_one<T, R, S, NT, kSeriesBoth>(a, s);
     default: return hipErrorInvalidValue;
   }

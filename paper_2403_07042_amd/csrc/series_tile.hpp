@@ -22,10 +22,14 @@
 // rounded once.
 //
 // What bounds it: at N = 2048 a pass moves 33.5 MB in and 33.5 MB out (a copy of
-// that size takes 8.4 us) and reads 0.4 GB of LDS; its loads, terms and stores
-// run one after another in a workgroup, and the launch is one round of them.
-// Measured: 22.8 + 21.8 us FP32 (three terms) and 45.6 + 45.1 us FP64 (four),
-// against 387 + 224 and 844 + 452 us of the dense products.
+// that size takes 8.4 us) and reads 0.4 GB of LDS per rotation; its loads, terms
+// and stores run one after another in a workgroup, and the launch is one round
+// of them.  Measured there: 21 + 20 us FP32 (three terms) and 48 + 48 us FP64
+// (four), against 387 + 224 and 844 + 452 us of the dense products; a folded
+// step in one pass (kSeriesStep) 32.8 us FP32 and 83.7 us FP64.  The rest of
+// the range, two passes / one: N = 100 9.0 / 5.8 us FP32 and 13.3 / 7.4 FP64,
+// 500 15.1 / 8.4 and 19.5 / 12.8, 1024 21.4 / 13.6 and 36.7 / 26.7, 4096 161 /
+// 152 and 611 / 540, 8190 1268 / 1171 and 4670 / 4566.
 #pragma once
 
 #include <cstdint>
@@ -41,6 +45,13 @@ namespace qme {
 __device__ __forceinline__ int series_group(int block, int groups) {
   const int per = (groups + 7) >> 3;
   return (block & 7) * per + (block >> 3);
+}
+
+// A value that every lane of the wave holds, kept in scalar registers.
+__device__ __forceinline__ double series_uniform(double x) {
+  const long long b = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_readfirstlane(int(b)), hi = __builtin_amdgcn_readfirstlane(int(b >> 32));
+  return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | unsigned(lo));
 }
 
 template <typename T>
@@ -64,23 +75,28 @@ __device__ __forceinline__ int64_t series_unit(int c, int g, int groups) {
 // MODE kSeriesBoth: as kSeriesFirst, and writes W's own rows too.
 // MODE kSeriesLower: reads those blocks, writes the rows of rho_u on and below
 // the diagonal.
-// MODE kSeriesFold: as kSeriesLower with the previous step's factor and the
-// decoherence factor applied, whole rows written, the diagonal before the
-// decoherence kept for the trace (CgemmArgs::fold_d).  Both triangles come
-// from their own rows here, so they agree to rounding only; the closing pass
-// of the call restores the exact symmetry (Herm commutes with every step).
+// MODE kSeriesFold: as kSeriesLower with the decoherence factor applied, whole
+// rows written, the diagonal before the decoherence kept for the trace
+// (CgemmArgs::fold_d).  Both triangles come from their own rows here, so they
+// agree to rounding only; the closing pass of the call restores the exact
+// symmetry (Herm commutes with every step).
+// MODE kSeriesStep: kSeriesFold and the next step's kSeriesFirst in one: a row
+// of the state is all that its own next pass needs, so it stays in the
+// registers and only the blocks pass through memory, once per step.
 //
-// Factors near one are applied as x + (small terms), the small terms in the
-// storage type and their coefficients formed in FP64, so that a result is
-// rounded once, at the last addition.
+// The renormalisation factor is a scalar: it stays pending (DissArgs::pend)
+// until the call's closing pass.  Factors near one are applied as x + (small
+// terms), the small terms and their coefficients in the storage type, so that a
+// result is rounded once, at the last addition.
 template <typename T, int R, int S, int NT, int MODE>
 __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, unsigned char *lds) {
   // (a batch's passes give each instance the bits of its own passes: the
   // arithmetic must not depend on what the compiler fuses in each shape)
 #pragma clang fp contract(off)
   typedef T unit __attribute__((ext_vector_type(R)));
-  constexpr bool kBlocks = MODE == kSeriesFirst || MODE == kSeriesBoth;   // reads rows, writes blocks
-  constexpr bool kRows = MODE != kSeriesFirst;                            // writes rows
+  constexpr bool kReadRows = MODE == kSeriesFirst || MODE == kSeriesBoth;
+  constexpr bool kBlocks = kReadRows || MODE == kSeriesStep;    // writes blocks
+  constexpr bool kRows = MODE == kSeriesLower || MODE == kSeriesFold || MODE == kSeriesBoth;   // writes rows
   // v in LDS: a unit's 16-byte parts (one or two) in planes of their own, so
   // that lanes with neighbouring slots read without bank conflicts; the
   // imaginary planes follow the real ones
@@ -137,8 +153,11 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
       to.val[i] = q[unsigned(i * 64 + lane)];
     }
   };
+  auto fetch_first = [&]() {
 #pragma unroll
-  for (int s = 0; s < B; ++s) fetch(buf[s], off[s]);
+    for (int s = 0; s < B; ++s) fetch(buf[s], off[s]);
+  };
+  fetch_first();
 
   // the rows, one state per lane.  A slot or row past the end repeats the
   // last one: no entry reads it and it is not written.
@@ -146,7 +165,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   unsigned col[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) col[s] = unsigned(a.slot_col[unsigned(min((wave * S + s) * 64 + lane, n - 1))]);
-  if constexpr (kBlocks) {
+  if constexpr (kReadRows) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const T *p_re = a.x_re + int64_t(row[r]) * a.ld, *p_im = a.x_im + int64_t(row[r]) * a.ld;
@@ -174,14 +193,16 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
       }
     }
   }
+  unit t_re[S], t_im[S];
+  const T sgn = T(a.sign), w1 = sgn * T(a.ratio[1]);
+  // the terms of x's rows, up to delta = (+-i w1 t)
+  auto rotate = [&]() {
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const int slot = (wave * S + s) * 64 + lane;
     put(lds, slot, x_re[s], x_im[s]);
   }
 
-  unit t_re[S], t_im[S];
-  const T sgn = T(a.sign);
   for (int k = a.order; k >= 1; --k) {
     __syncthreads();
 #pragma unroll
@@ -189,6 +210,9 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
 #pragma unroll
       for (int r = 0; r < R; ++r) t_re[s][r] = t_im[s][r] = T(0);
       auto add = [&](T val, int at) {
+        // (planes beyond the reach of a read's offset: their addresses formed
+        // here, not kept for every entry and term)
+        if constexpr ((2 * P - 1) * kPlane > 65535) asm volatile("" : "+v"(at));
 #pragma unroll
         for (int p = 0; p < P; ++p) {
           const part g_re = *reinterpret_cast<const part *>(lds + at + p * kPlane);
@@ -238,53 +262,80 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
       put(lds, slot, n_re, n_im);
     }
   }
+  };
+  // t <- d, the small part of the result x + d
+  auto finish = [&]() {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const unit was = t_re[s];
+      t_re[s] = -w1 * t_im[s];
+      t_im[s] = w1 * was;
+    }
+    if (a.phase) {   // (1 + q)(x + d)
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const T q_re = T(a.phase[2 * col[s]]), q_im = sgn * T(a.phase[2 * col[s] + 1]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const T yr = x_re[s][r] + t_re[s][r], yi = x_im[s][r] + t_im[s][r];
+          t_re[s][r] = series_fma<T>(-q_im, yi, series_fma<T>(q_re, yr, t_re[s][r]));
+          t_im[s][r] = series_fma<T>(q_im, yr, series_fma<T>(q_re, yi, t_im[s][r]));
+        }
+      }
+    }
+  };
 
+  auto decohere = [&]() {
+    // x <- the decoherence step of the rotated rows
+    double row_d[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      row_d[r] = series_uniform(-0.5 * a.fold_dt * a.fold_d[row[r]]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const double col_d = -0.5 * a.fold_dt * a.fold_d[col[s]];
+      // (the trace is taken of the diagonal as it is stored)
+      T diag = T(0);
+      bool own = false;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const bool here = unsigned(row[r]) == col[s] && q0 + r < n;
+        own = own || here;
+        diag = here ? x_re[s][r] + t_re[s][r] : diag;
+      }
+      if (own && (wave * S + s) * 64 + lane < n) a.zdiag[col[s]] = double(diag);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double f = row_d[r] + col_d;
+        const double zr = double(x_re[s][r]) + double(t_re[s][r]);
+        const double zi = double(x_im[s][r]) + double(t_im[s][r]);
+        x_re[s][r] = T(__builtin_fma(f, zr, zr));
+        x_im[s][r] = T(__builtin_fma(f, zi, zi));
+      }
+    }
+  };
+
+  rotate();
+  finish();
+  if constexpr (MODE == kSeriesFold || MODE == kSeriesStep) decohere();
+  if constexpr (MODE == kSeriesStep) {
+    fetch_first();
+    __syncthreads();   // every wave has read v
+    rotate();
+    finish();
+  }
   // (the row passes hand their results to LDS, by state, so that the rows are
   // written in order: the slots' order would leave parts of lines)
   if constexpr (kRows) __syncthreads();
-  const T w1 = sgn * T(a.ratio[1]);
-  double eps = 0.0;                    // the previous step's factor less 1
-  double row_d[R];
-  if constexpr (MODE == kSeriesFold) {
-    if (a.scale) eps = *a.scale - 1.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) row_d[r] = 0.5 * a.fold_dt * a.fold_d[row[r]];
-  }
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const int slot = (wave * S + s) * 64 + lane;
     if (slot >= n) continue;
     const unsigned c = col[s];
-    T q_re = T(0), q_im = T(0);
-    if (a.phase) {
-      q_re = T(a.phase[2 * c]);
-      q_im = sgn * T(a.phase[2 * c + 1]);
-    }
-    double col_d = 0.0;
-    if constexpr (MODE == kSeriesFold) col_d = 0.5 * a.fold_dt * a.fold_d[c];
-    unit w_re, w_im;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const T xr = x_re[s][r], xi = x_im[s][r];
-      T dr = -w1 * t_im[s][r], di = w1 * t_re[s][r];   // result = x + d
-      if (a.phase) {   // (1 + q)(x + d)
-        const T yr = xr + dr, yi = xi + di;
-        dr = series_fma<T>(-q_im, yi, series_fma<T>(q_re, yr, dr));
-        di = series_fma<T>(q_im, yr, series_fma<T>(q_re, yi, di));
-      }
-      if constexpr (MODE != kSeriesFold) {
-        w_re[r] = xr + dr;
-        w_im[r] = xi + di;
-      } else {
-        // (1 + eps)(1 - phi)(x + d)
-        // (the trace is taken of the diagonal as it is stored)
-        if (unsigned(row[r]) == c && q0 + r < n)
-          a.zdiag[c] = double(xr + series_fma<T>(T(eps), xr + dr, dr));
-        const double phi = row_d[r] + col_d;
-        const T f = T(eps - phi - eps * phi);
-        w_re[r] = xr + series_fma<T>(f, xr + dr, dr);
-        w_im[r] = xi + series_fma<T>(f, xi + di, di);
-      }
+    unit w_re = x_re[s], w_im = x_im[s];
+    if constexpr (MODE != kSeriesFold) {
+      w_re += t_re[s];
+      w_im += t_im[s];
     }
     if constexpr (kBlocks) {
       const int64_t u = series_unit(0, group, groups);

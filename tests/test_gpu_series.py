@@ -81,6 +81,29 @@ def test_shape_edges_against_dense(n, precision, fold):
     check(run(wl, precision, 1, (3, 4), rho0, fold), run(wl, precision, 0, (3, 4), rho0, fold), precision)
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [33, 256, 257, 1025, 2049, 4097, 5121])
+def test_one_pass_steps_equal_profiled_steps(n, precision):
+    """A step in one pass is the arithmetic of its two passes (which a profiled
+    call runs): the same bits, over odd and even counts of steps."""
+    wl = cavity_chain(n)
+    psi = W.haar_psi(n, 3)
+    print(f"one-pass steps N={n} {precision}", flush=True)
+    got = []
+    for profiled in (False, True):
+        sol = P.Solver(wl, precision)
+        sol.set_products(1)
+        sol.set_rho(np.outer(psi, psi.conj()), sink=0.125)
+        if profiled:
+            sol.profile(True)
+        for k in (1, 2, 3):
+            sol.step(k)
+        got.append((*sol.get_rho(), sol.observe()[1]))
+        sol.close()
+    assert np.array_equal(got[0][0], got[1][0])
+    assert got[0][1:] == got[1][1:]
+
+
 @pytest.mark.parametrize("n,precision", [(4095, "fp32"), (4097, "fp32"), (5120, "fp32"), (5121, "fp32"),
                                          (4097, "fp64")])
 def test_large_shapes_against_dense(n, precision):
