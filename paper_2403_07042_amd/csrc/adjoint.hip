@@ -191,7 +191,10 @@ __global__ __launch_bounds__(kAdjThreads) void adj_dissipate_kernel(AdjArgs<T> p
     }
     if (first) {
       const double rs = wave_sum(e);
-      if (c == 0 && u < n) p.rowbuf[int64_t(bj) * n + u] = rs;
+      if (c == 0 && u < n) {
+        double *at = p.rowbuf + int64_t(bj) * n + u;
+        *at = p.add ? *at + rs : rs;
+      }
     }
    }
   }
@@ -207,12 +210,14 @@ __global__ __launch_bounds__(kAdjThreads) void adj_dissipate_kernel(AdjArgs<T> p
   if (first && r0 == 0 && v < n) {
     double sacc = 0.0;
     for (int w = 0; w < kAdjThreads / TD; ++w) sacc += s_col[w][c];
-    p.colbuf[int64_t(bi) * n + v] = sacc;
+    double *at = p.colbuf + int64_t(bi) * n + v;
+    *at = p.add ? *at + sacc : sacc;
   }
   if (int(threadIdx.x) < na) {
     double sacc = 0.0;
     for (int w = 0; w < kAdjThreads / TD; ++w) sacc += s_g[w][threadIdx.x];
-    p.gbuf[int64_t(blockIdx.x) * p.n_arrival + a0 + threadIdx.x] = sacc;
+    double *at = p.gbuf + int64_t(blockIdx.x) * p.n_arrival + a0 + threadIdx.x;
+    *at = p.add ? *at + sacc : sacc;
   }
   if (!first || diag_tile) return;
   // mirror tile (bj, bi) of mu
@@ -365,7 +370,12 @@ __global__ void set_diag_kernel(T *x_re, T *x_im, int64_t ld, int64_t n, const d
 // W = L(B, G) for B = -i tau H by the series of the adjoint of the Frechet
 // derivative of exp: M_1 = G, R_1 = G B, M_{k+1} = (B M_k + R_k) / (k+1),
 // R_{k+1} = R_k B / (k+1), W = sum_k M_k.  H is sparse (CSR, symmetric), so
-// every product is a sparse-times-dense pass.
+// every product is a sparse-times-dense pass, one workgroup per 32 x 32 tile:
+// of all tiles, or of the listed ones (frechet_tiles: elsewhere G is zero and
+// nothing reaches W's entries), where the planes hold zeros in the others.
+// Over all tiles at N = 2048 a term moves 470 MB (62 + 73 us as a right and a
+// left pass); listed (a fifth of the tiles), and both in one, it takes 33 us,
+// bound by the latency of its chains of loads: 1.14 -> 0.35 ms per call.
 
 template <typename T>
 __global__ void widen_kernel(const T *gr, const T *gi, double *dr, double *di, int64_t total) {
@@ -376,48 +386,71 @@ __global__ void widen_kernel(const T *gr, const T *gi, double *dr, double *di, i
   }
 }
 
-// out = inv (B X + R), W += out      (row i of B X uses row i of H)
-__global__ void frechet_left_kernel(const int64_t *ptr, const int32_t *col, const double *val,
-                                    double tau, const double *xr, const double *xi,
-                                    const double *rr, const double *ri, double *outr,
-                                    double *outi, double *wr, double *wi, int64_t n, int64_t ld,
-                                    double inv) {
-  const int64_t i = blockIdx.y;
-  const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  double ar = 0.0, ai = 0.0;
-  for (int64_t q = ptr[i]; q < ptr[i + 1]; ++q) {
-    const int64_t o = int64_t(col[q]) * ld + j;
-    ar += val[q] * xr[o];
-    ai += val[q] * xi[o];
-  }
-  const int64_t o = i * ld + j;
-  // B X = -i tau (H X): real part tau Im(HX), imaginary part -tau Re(HX)
-  const double vr = inv * (tau * ai + rr[o]);
-  const double vi = inv * (-tau * ar + ri[o]);
-  outr[o] = vr;
-  outi[o] = vi;
-  wr[o] += vr;
-  wi[o] += vi;
+// The element of a thread in its workgroup's 32 x 32 tile: listed (row and
+// column tile in 16 bits each), or of the whole grid.
+__device__ __forceinline__ void frechet_tile(const int32_t *listed, int64_t &i, int64_t &j) {
+  const int bi = listed ? listed[blockIdx.x] >> 16 : int(blockIdx.y);
+  const int bj = listed ? listed[blockIdx.x] & 65535 : int(blockIdx.x);
+  i = int64_t(bi) * 32 + (threadIdx.x >> 5);
+  j = int64_t(bj) * 32 + (threadIdx.x & 31);
 }
 
-// out = inv X B                      ((X H)[i][j] = sum over row j of H)
-__global__ void frechet_right_kernel(const int64_t *ptr, const int32_t *col, const double *val,
-                                     double tau, const double *xr, const double *xi,
-                                     double *outr, double *outi, int64_t n, int64_t ld,
-                                     double inv) {
-  const int64_t i = blockIdx.y;
-  const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  double ar = 0.0, ai = 0.0;
+// (X H)[i][j], the sum over row j of H
+__device__ __forceinline__ void frechet_right(const int64_t *ptr, const int32_t *col,
+                                              const double *val, const double *xr,
+                                              const double *xi, int64_t i, int64_t j, int64_t ld,
+                                              double &ar, double &ai) {
+  ar = ai = 0.0;
   for (int64_t q = ptr[j]; q < ptr[j + 1]; ++q) {
     const int64_t o = i * ld + col[q];
     ar += val[q] * xr[o];
     ai += val[q] * xi[o];
   }
+}
+
+// W = M (G widened), R = M B
+__global__ __launch_bounds__(1024) void frechet_begin_kernel(
+    const int64_t *ptr, const int32_t *col, const double *val, const int32_t *listed, double tau,
+    const double *mr, const double *mi, double *rr, double *ri, double *wr, double *wi, int64_t n,
+    int64_t ld) {
+  int64_t i, j;
+  frechet_tile(listed, i, j);
+  if (i >= n || j >= n) return;
+  double ar, ai;
+  frechet_right(ptr, col, val, mr, mi, i, j, ld, ar, ai);
   const int64_t o = i * ld + j;
-  outr[o] = inv * tau * ai;
-  outi[o] = -inv * tau * ar;
+  rr[o] = tau * ai;
+  ri[o] = -tau * ar;
+  wr[o] = mr[o];
+  wi[o] = mi[o];
+}
+
+// M' = inv (B M + R), W += M', R' = inv R B    (row i of B M uses row i of H;
+// B M = -i tau (H M): real part tau Im(HM), imaginary part -tau Re(HM))
+__global__ __launch_bounds__(1024) void frechet_term_kernel(
+    const int64_t *ptr, const int32_t *col, const double *val, const int32_t *listed, double tau,
+    const double *mr, const double *mi, const double *rr, const double *ri, double *m2r,
+    double *m2i, double *r2r, double *r2i, double *wr, double *wi, int64_t n, int64_t ld,
+    double inv) {
+  int64_t i, j;
+  frechet_tile(listed, i, j);
+  if (i >= n || j >= n) return;
+  double ar = 0.0, ai = 0.0;
+  for (int64_t q = ptr[i]; q < ptr[i + 1]; ++q) {
+    const int64_t o = int64_t(col[q]) * ld + j;
+    ar += val[q] * mr[o];
+    ai += val[q] * mi[o];
+  }
+  const int64_t o = i * ld + j;
+  const double vr = inv * (tau * ai + rr[o]);
+  const double vi = inv * (-tau * ar + ri[o]);
+  m2r[o] = vr;
+  m2i[o] = vi;
+  wr[o] += vr;
+  wi[o] += vi;
+  frechet_right(ptr, col, val, rr, ri, i, j, ld, ar, ai);
+  r2r[o] = inv * tau * ai;
+  r2i[o] = -inv * tau * ar;
 }
 
 // out[e] = Im W[col_e][row_e] * val_e  (tr(W H_p) gathers W transposed)
@@ -651,7 +684,7 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
   // = sum rho X = sum rho V^dag only the tiles that reach the gradient.
   // N = 2048 lattice, per adjoint step: 387 + 224 us of products -> 26 + 19 us
   // of passes, G 407 -> 97 us (a fifth of the tiles, 0.7 of the FP32 matrix
-  // rate); the whole step 1157 -> 276 us.
+  // rate); the whole step 1157 -> 262 us.
   auto [b_re, b_im] = planes(L.Y);
   int32_t *listed = reinterpret_cast<int32_t *>(ws + L.listed);
   if (series) {
@@ -702,9 +735,7 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
       aa.z_re = z_re;
       aa.z_im = z_im;
       ADJ_OK(launch_adj_dissipate<T>(aa, s));
-      ADJ_OK(launch_q_reduce(aa.rowbuf, aa.colbuf, n, q, s));
-      ADJ_OK(launch_gamma_reduce(aa.gbuf, L.blocks, c->n_arrival, c->arrival_of, c->ada, q, n,
-                                 nj, c->model.dt, ggam, s));
+      aa.add = 1;
       sa.z_re = z_re;
       sa.z_im = z_im;
       ADJ_OK(launch_adj_sparse_gamma<T>(sa, s));
@@ -731,6 +762,13 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
 
   phase.reset();
   phase.emplace("qme_adjoint: Frechet finalisation");
+  // the rates' sums over all steps, reduced once (per step the two passes cost
+  // 9.4 us at N = 2048)
+  if (n_steps > 0) {
+    ADJ_OK(launch_q_reduce(aa.rowbuf, aa.colbuf, n, q, s));
+    ADJ_OK(launch_gamma_reduce(aa.gbuf, L.blocks, c->n_arrival, c->arrival_of, c->ada, q, n, nj,
+                               c->model.dt, ggam, s));
+  }
   std::vector<double> gam(std::max(1, nj));
   ADJ_OK(hipMemcpyAsync(gam.data(), ggam, sizeof(double) * gam.size(), hipMemcpyDeviceToHost, s));
   const size_t n_terms = c->term_offset.size() - 1;
@@ -748,15 +786,17 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
     auto [r_re, r_im] = dpl(L.fr);
     auto [r2_re, r2_im] = dpl(L.fr2);
     const int64_t total = int64_t(pe);
-    const dim3 eb(256), eg(unsigned((total + 255) / 256));
+    const dim3 eb(256), eg(unsigned((total + 255) / 256)), tb(1024);
     hipLaunchKernelGGL(widen_kernel<T>, eg, eb, 0, s, g_re, g_im, m_re, m_im, total);
     ADJ_OK(hipGetLastError());
-    hipLaunchKernelGGL(widen_kernel<T>, eg, eb, 0, s, g_re, g_im, w_re, w_im, total);
-    ADJ_OK(hipGetLastError());
     const double tau = dt;
-    const dim3 sg(unsigned((n + 255) / 256), unsigned(n));
-    hipLaunchKernelGGL(frechet_right_kernel, sg, eb, 0, s, c->h_ptr, c->h_col, c->h_val, tau,
-                       m_re, m_im, r_re, r_im, n, ld, 1.0);
+    const int32_t *tiles = series ? listed : nullptr;
+    const unsigned edge = unsigned((n + 31) / 32);
+    const dim3 sg = series ? dim3(unsigned(c->adj_tiles.size())) : dim3(edge, edge);
+    if (series)   // (M holds all of G, zeros outside the listed tiles)
+      for (double *p : {r_re, m2_re, r2_re}) ADJ_OK(hipMemsetAsync(p, 0, 2 * pe * sizeof(double), s));
+    hipLaunchKernelGGL(frechet_begin_kernel, sg, tb, 0, s, c->h_ptr, c->h_col, c->h_val, tiles, tau,
+                       m_re, m_im, r_re, r_im, w_re, w_im, n, ld);
     ADJ_OK(hipGetLastError());
     // number of terms: theta^k / k! below 1e-18 with theta = tau |H|_1
     const double theta = tau * c->h_norm1;
@@ -767,11 +807,9 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
     }
     for (int k = 1; k <= kmax; ++k) {
       const double inv = 1.0 / double(k + 1);
-      hipLaunchKernelGGL(frechet_left_kernel, sg, eb, 0, s, c->h_ptr, c->h_col, c->h_val, tau,
-                         m_re, m_im, r_re, r_im, m2_re, m2_im, w_re, w_im, n, ld, inv);
-      ADJ_OK(hipGetLastError());
-      hipLaunchKernelGGL(frechet_right_kernel, sg, eb, 0, s, c->h_ptr, c->h_col, c->h_val, tau,
-                         r_re, r_im, r2_re, r2_im, n, ld, inv);
+      hipLaunchKernelGGL(frechet_term_kernel, sg, tb, 0, s, c->h_ptr, c->h_col, c->h_val, tiles,
+                         tau, m_re, m_im, r_re, r_im, m2_re, m2_im, r2_re, r2_im, w_re, w_im, n,
+                         ld, inv);
       ADJ_OK(hipGetLastError());
       std::swap(m_re, m2_re);
       std::swap(m_im, m2_im);

@@ -333,6 +333,7 @@ struct AdjArgs {
   double *rowbuf;        // [tiles * n]
   double *colbuf;        // [tiles * n]
   double *gbuf;          // [blocks * n_arrival]
+  int32_t add = 0;       // 1: the three buffers' sums go on from the steps before
   // sparse (non-monomial) channels: rows of A^T (csrt_ptr [n_csr][n + 1],
   // row k: the images u of preimage k with their unit-rate coefficients),
   // the rates, and K's off-diagonal part (nullptr: none), as in DissArgs:
