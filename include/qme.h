@@ -564,10 +564,7 @@ qme_status qme_set_fused(qme_ctx *ctx, int32_t enable);
  * precision: one pass per step rotates each row, applies the factor and starts
  * the next step's rotation, and the renormalisation factor stays pending until
  * the call's closing pass.  (A profiled call, qme_profile_enable, runs a step's
- * two passes: the same arithmetic.)  With operators that map onto other basis
- * states, such steps of systems of 64 to 256 states (FP64: 1024) in calls of
- * several take the decoherence step as the next pass loads; the call's last
- * step ends with the decoherence pass.  enable: 0 or 1, else QME_E_ARG. */
+ * two passes: the same arithmetic.)  enable: 0 or 1, else QME_E_ARG. */
 qme_status qme_set_fold(qme_ctx *ctx, int32_t enable);
 
 /* Tile body of the FP32 products whose second operand is read by rows (all

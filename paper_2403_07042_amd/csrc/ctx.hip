@@ -512,81 +512,14 @@ static hipError_t fold_steps(qme_ctx *c, void *state, int64_t n_steps, void *ws,
   return n_steps > 0 ? launch_apply_scale<T>(x_re, x_im, int64_t(pe), aux + 4, s) : hipSuccess;
 }
 
-// Steps of models whose decoherence operators act inside the basis, by the
-// series: the decoherence step of a rotated state (kept as whole rows) is taken
-// by the next step's first pass as it loads, and the trace formed beside it,
-// its factor pending; the last step's by the decoherence pass, which restores
-// the exact symmetry (as series_fold_steps).  Two launches and two round trips
-// of the state per step in place of four and three; the gathered rows come as
-// single elements, which costs more as N grows.  Per step, fused against the
-// passes: N = 64 13.8 / 15.9 us FP32 and 13.6 / 17.9 FP64, 144 16.2 / 17.6 and
-// 15.5 / 19.8, 256 17.8 / 19.7 and 15.6 / 20.6, 512 24.6 / 23.3 and 26.0 / 30.1,
-// 1000 38.2 / 37.9 and 45.3 / 49.5; beyond that it loses in both (N = 1728 FP32
-// 74 / 69).  Systems below 64 states keep the pass in every step.
-static bool uses_gather_fold(const qme_ctx *c, int64_t n_steps) {
-  const int64_t most = c->precision == QME_FP64 ? kSeriesGatherMaxN : 256;
-  return c->fold && uses_series(c) && c->jt.n_gather > 0 && c->jt.n_csr == 0 &&
-         c->jt.koff_col.empty() && c->n >= 64 && c->n <= most && n_steps > 1;
-}
-
-template <typename T>
-static hipError_t series_gather_steps(qme_ctx *c, void *state, int64_t n_steps, void *ws,
-                                      hipStream_t s) {
-  const size_t pe = plane_elems(c);
-  T *x_re = static_cast<T *>(state), *x_im = x_re + pe;
-  double *aux = reinterpret_cast<double *>(x_im + pe);
-  T *y_re = static_cast<T *>(ws), *y_im = y_re + pe;
-  T *z_re = y_im + pe, *z_im = z_re + pe;
-  double *zdiag = reinterpret_cast<double *>(static_cast<char *>(ws) +
-                                             align256(4 * pe * sizeof(T)));
-  DissArgs<T> da{z_re, z_im, x_re, x_im, c->ld, c->n, c->model.dt, c->d, c->leak,
-                 c->pi, c->cg, c->jt.n_gather, aux, aux, c->trw, zdiag};
-  c->sparse_args(da);
-  for (int64_t k = 0; k < n_steps; ++k) {
-    SeriesArgs<T> first = k == 0 ? series_args<T>(c, x_re, x_im, y_re, y_im, 1, false)
-                                 : series_args<T>(c, z_re, z_im, y_re, y_im, 1, false);
-    first.fold_d = c->d;
-    first.fold_dt = c->model.dt;
-    if (k > 0) {
-      first.pi = c->pi;
-      first.cg = c->cg;
-      first.n_gather = c->jt.n_gather;
-      first.self_mask = c->self_mask;
-      first.tr_zdiag = zdiag;
-      first.tr_w = c->trw;
-      first.tr_leak = c->leak;
-      first.tr_aux = aux;
-      first.tr_dt = c->model.dt;
-      first.tr_pend = k > 1 ? aux + 4 : nullptr;
-    }
-    SeriesArgs<T> second = series_args<T>(c, y_re, y_im, z_re, z_im, 1, false);
-    second.zdiag = zdiag;
-    hipError_t e = mark(c, s, -1);
-    if (e == hipSuccess) e = launch_series_pass<T>(first, k == 0 ? kSeriesFirst : kSeriesGather, s);
-    if (e == hipSuccess) e = mark(c, s, 0);
-    if (e == hipSuccess) e = launch_series_pass<T>(second, kSeriesFold, s);
-    if (e == hipSuccess) e = mark(c, s, 1);
-    if (k == n_steps - 1) {
-      da.pend = k > 0 ? aux + 4 : nullptr;
-      if (e == hipSuccess) e = launch_trace<T>(da, s);
-      if (e == hipSuccess) e = mark(c, s, 2);
-      if (e == hipSuccess) e = launch_dissipate<T>(da, s);
-      if (e == hipSuccess) e = mark(c, s, 3);
-    }
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
 template <typename T>
 static qme_status step_impl(qme_ctx *c, void *state, int64_t n_steps, void *ws,
                             hipStream_t s) {
   const TimerScope timer_scope;
   const size_t pe = plane_elems(c);
-  if (!uses_small_path(c) && (uses_fold(c) || uses_gather_fold(c, n_steps))) {
-    hipError_t e = !uses_fold(c)  ? series_gather_steps<T>(c, state, n_steps, ws, s)
-                   : uses_series(c) ? series_fold_steps<T>(c, state, n_steps, ws, s)
-                                    : fold_steps<T>(c, state, n_steps, ws, s);
+  if (!uses_small_path(c) && uses_fold(c)) {
+    hipError_t e = uses_series(c) ? series_fold_steps<T>(c, state, n_steps, ws, s)
+                                   : fold_steps<T>(c, state, n_steps, ws, s);
     if (e != hipSuccess) {
       set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
       return QME_E_DEVICE;

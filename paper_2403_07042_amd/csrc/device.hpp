@@ -399,12 +399,10 @@ enum {
   kSeriesLower = 1,
   kSeriesFold = 2,
   kSeriesBoth = 3,
-  kSeriesGather = 4,
-  kSeriesStep = 5
+  kSeriesStep = 4
 };
 constexpr int kSeriesMaxOrder = 24;   // as kMaxSeriesOrder of the plan
 constexpr int64_t kSeriesMaxN = 8192;   // the rows of a workgroup fit its LDS
-constexpr int64_t kSeriesGatherMaxN = 1024;   // kSeriesGather is built up to here (uses_gather_fold)
 template <typename T>
 struct SeriesArgs {
   const T *x_re, *x_im;      // ld x ld, rows and columns < n read
@@ -426,13 +424,7 @@ struct SeriesArgs {
   const double *tr_zdiag = nullptr, *tr_w = nullptr, *tr_leak = nullptr, *tr_pend = nullptr;
   double *tr_aux = nullptr;
   double tr_dt = 0.0;
-  // kSeriesGather: the gather channels (as DissArgs)
-  const int32_t *pi = nullptr;
-  const double *cg = nullptr;
-  int32_t n_gather = 0;
-  uint32_t self_mask = 0;
-  // kSeriesFold, kSeriesStep, kSeriesGather (as CgemmArgs::fold_*; without
-  // fold_d: no decoherence factor)
+  // kSeriesFold, kSeriesStep (as CgemmArgs::fold_*)
   const double *fold_d = nullptr;
   double fold_dt = 0.0;
   double *zdiag = nullptr;

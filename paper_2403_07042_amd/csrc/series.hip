@@ -102,9 +102,6 @@ hipError_t launch_mode(const SeriesArgs<T> &a, int mode, hipStream_t s) {
     case kSeriesLower: return launch_one<T, R, S, NT, kSeriesLower>(a, s);
     case kSeriesFold: return launch_one<T, R, S, NT, kSeriesFold>(a, s);
     case kSeriesStep: return launch_one<T, R, S, NT, kSeriesStep>(a, s);
-    case kSeriesGather:
-      if constexpr (S * NT <= kSeriesGatherMaxN) return launch_one<T, R, S, NT, kSeriesGather>(a, s);
-      else return hipErrorInvalidValue;
     case kSeriesBoth: return launch_one<T, R, S, NT, kSeriesBoth>(a, s);
     default: return hipErrorInvalidValue;
   }

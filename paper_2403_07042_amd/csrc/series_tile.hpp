@@ -72,9 +72,6 @@ __device__ __forceinline__ int64_t series_unit(int c, int g, int groups) {
 }
 
 // MODE kSeriesFirst: reads the state, writes W^dag in blocks (series_unit).
-// MODE kSeriesGather: as kSeriesFirst on the decoherence step (DissArgs) of a
-// rotated state whose rows are whole, unscaled: every row takes the rows that
-// the channels move onto it, along with its own.
 // MODE kSeriesBoth: as kSeriesFirst, and writes W's own rows too.
 // MODE kSeriesLower: reads those blocks, writes the rows of rho_u on and below
 // the diagonal.
@@ -97,7 +94,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   // arithmetic must not depend on what the compiler fuses in each shape)
 #pragma clang fp contract(off)
   typedef T unit __attribute__((ext_vector_type(R)));
-  constexpr bool kReadRows = MODE == kSeriesFirst || MODE == kSeriesBoth || MODE == kSeriesGather;
+  constexpr bool kReadRows = MODE == kSeriesFirst || MODE == kSeriesBoth;
   constexpr bool kBlocks = kReadRows || MODE == kSeriesStep;    // writes blocks
   constexpr bool kRows = MODE == kSeriesLower || MODE == kSeriesFold || MODE == kSeriesBoth;   // writes rows
   // v in LDS: a unit's 16-byte parts (one or two) in planes of their own, so
@@ -193,60 +190,6 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
       for (int s = 0; s < S; ++s) {
         x_re[s][r] = p_re[at[s]];
         x_im[s][r] = p_im[at[s]];
-      }
-    }
-  }
-  if constexpr (MODE == kSeriesGather) {
-    // x <- x + small terms: -dt/2 (d_u + d_v) x, and dt c_u c_v times the
-    // element of each channel's row and column (its own for a channel that maps
-    // every state to itself), in FP64
-    double g_re[S][R], g_im[S][R];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const double col_d = -0.5 * a.fold_dt * a.fold_d[col[s]];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double w = __builtin_fma(-0.5 * a.fold_dt, a.fold_d[row[r]], col_d);
-        g_re[s][r] = w * double(x_re[s][r]);
-        g_im[s][r] = w * double(x_im[s][r]);
-      }
-    }
-    for (int j = 0; j < a.n_gather; ++j) {
-      const int32_t *pi = a.pi + int64_t(j) * n;
-      const double *cg = a.cg + int64_t(j) * n;
-      const bool self = (a.self_mask >> (j & 31)) & 1u && j < 32;
-      int pc[S];
-      double cc[S];
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        pc[s] = pi[col[s]];
-        cc[s] = pc[s] < 0 ? 0.0 : a.fold_dt * cg[col[s]];
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int pr = __builtin_amdgcn_readfirstlane(pi[row[r]]);
-        if (pr < 0) continue;
-        const double cr = cg[row[r]];
-        const T *p_re = a.x_re + int64_t(pr) * a.ld, *p_im = a.x_im + int64_t(pr) * a.ld;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          T from_re = x_re[s][r], from_im = x_im[s][r];
-          if (!self) {
-            from_re = p_re[unsigned(max(pc[s], 0))];
-            from_im = p_im[unsigned(max(pc[s], 0))];
-          }
-          const double w = cr * cc[s];
-          g_re[s][r] = __builtin_fma(w, pc[s] < 0 ? 0.0 : double(from_re), g_re[s][r]);
-          g_im[s][r] = __builtin_fma(w, pc[s] < 0 ? 0.0 : double(from_im), g_im[s][r]);
-        }
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        x_re[s][r] = T(double(x_re[s][r]) + g_re[s][r]);
-        x_im[s][r] = T(double(x_im[s][r]) + g_im[s][r]);
       }
     }
   }
@@ -347,10 +290,10 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
     double row_d[R];
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      row_d[r] = series_uniform(a.fold_d ? -0.5 * a.fold_dt * a.fold_d[row[r]] : 0.0);
+      row_d[r] = series_uniform(-0.5 * a.fold_dt * a.fold_d[row[r]]);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const double col_d = a.fold_d ? -0.5 * a.fold_dt * a.fold_d[col[s]] : 0.0;
+      const double col_d = -0.5 * a.fold_dt * a.fold_d[col[s]];
       // (the trace is taken of the diagonal as it is stored)
       T diag = T(0);
       bool own = false;

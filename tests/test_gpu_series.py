@@ -104,37 +104,6 @@ def test_one_pass_steps_equal_profiled_steps(n, precision):
     assert got[0][1:] == got[1][1:]
 
 
-@pytest.mark.parametrize("precision", ["fp32", "fp64"])
-@pytest.mark.parametrize("atoms,cap", [([1, 1], 3), ([2, 2], 2), ([2, 2], 3), ([1, 1, 1], 3), ([1, 1, 1], 4)])
-def test_gather_on_load_against_the_pass(atoms, cap, precision):
-    """Multi-step calls that take the decoherence step (jumps inside the basis
-    and dephasing) as the next pass loads, against the pass in every step: N =
-    64, 144, 256, 512 and 1000.  Both round a step's results a few times (at
-    most eight here) in half units of the last place."""
-    jumps = [(W.PHOTON_LEAK, c, -1, 0.2) for c in range(len(atoms))]
-    jumps += [(W.ATOM_DEPHASE, c, 0, 0.1) for c in range(len(atoms))]
-    wl = {"atoms": atoms, "photon_cap": [cap] * len(atoms), "exc_min": 0, "exc_max": -1,
-          "omega_c": [1.0] * len(atoms), "omega_a": [1.0] * sum(atoms), "g": [0.05] * sum(atoms),
-          "hops": [(c, c + 1, 0.05) for c in range(len(atoms) - 1)], "jumps": jumps, "dt": 0.05}
-    print(f"gather on load {atoms} cap {cap} {precision}", flush=True)
-    got = []
-    for fold in (True, False):
-        sol = P.Solver(wl, precision)
-        psi = W.haar_psi(sol.n, 5)
-        sol.set_products(1)
-        sol.set_fold(fold)
-        sol.set_rho(np.outer(psi, psi.conj()), sink=0.125)
-        for k in (2, 1, 5):
-            sol.step(k)
-        got.append((*sol.get_rho(), sol.observe()[1]))
-        sol.close()
-    eps = np.finfo(np.float32 if precision == "fp32" else np.float64).eps
-    tol = 8 * 8 * 2 * eps
-    assert np.array_equal(got[0][0], got[0][0].conj().T)
-    assert np.abs(got[0][0] - got[1][0]).max() < tol * np.abs(got[1][0]).max()
-    assert abs(got[0][1] - got[1][1]) < tol and abs(got[0][2] - got[1][2]) < tol
-
-
 @pytest.mark.parametrize("n,precision", [(4095, "fp32"), (4097, "fp32"), (5120, "fp32"), (5121, "fp32"),
                                          (4097, "fp64")])
 def test_large_shapes_against_dense(n, precision):
