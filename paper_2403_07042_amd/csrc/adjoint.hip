@@ -663,7 +663,7 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
   }
   // objective
   double *diag = reinterpret_cast<double *>(ws + L.diag);
-  ADJ_OK(launch_diag<T>(reinterpret_cast<const T *>(S), c->ld, n, diag, s));
+  ADJ_OK(launch_diag<T>(reinterpret_cast<const T *>(S), c->ld, n, nullptr, diag, s));
   std::vector<double> pops(n);
   ADJ_OK(hipMemcpyAsync(pops.data(), diag, sizeof(double) * n, hipMemcpyDeviceToHost, s));
   ADJ_OK(hipStreamSynchronize(s));

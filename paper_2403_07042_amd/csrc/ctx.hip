@@ -694,7 +694,7 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
   }
   HIP_OK(hipMalloc(&c->d, sizeof(double) * n));
   HIP_OK(hipMalloc(&c->leak, sizeof(double) * n));
-  HIP_OK(hipMalloc(&c->diag, sizeof(double) * (n + 8)));
+  HIP_OK(hipHostMalloc(reinterpret_cast<void **>(&c->diag), sizeof(double) * (n + 8)));
   HIP_OK(hipMemcpy(c->d, c->jt.d.data(), sizeof(double) * n, hipMemcpyHostToDevice));
   HIP_OK(hipMemcpy(c->leak, c->jt.leak.data(), sizeof(double) * n, hipMemcpyHostToDevice));
   {
@@ -1337,22 +1337,20 @@ extern "C" qme_status qme_observe(const qme_ctx *c, const void *state, double *p
   if (st != QME_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const size_t pe = plane_elems(c);
+  const double *aux = reinterpret_cast<const double *>(static_cast<const char *>(state) + 2 * pe * c->elem);
   hipError_t e;
-  if (c->elem == 8) e = launch_diag<double>(static_cast<const double *>(state), c->ld, c->n, c->diag, s);
-  else e = launch_diag<float>(static_cast<const float *>(state), c->ld, c->n, c->diag, s);
+  if (c->elem == 8) e = launch_diag<double>(static_cast<const double *>(state), c->ld, c->n, aux, c->diag, s);
+  else e = launch_diag<float>(static_cast<const float *>(state), c->ld, c->n, aux, c->diag, s);
   if (e != hipSuccess) { set_error(hipGetErrorString(e)); return QME_E_DEVICE; }
-  std::vector<double> host(c->n + 8);
-  const char *auxp = static_cast<const char *>(state) + 2 * pe * c->elem;
-  HIP_OK(hipMemcpyAsync(host.data(), c->diag, sizeof(double) * c->n, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(host.data() + c->n, auxp, 64, hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
+  const double *host = c->diag;
   double tr = 0.0;
   bool finite = true;
   for (int64_t u = 0; u < c->n; ++u) {
     tr += host[u];
     finite = finite && std::isfinite(host[u]);
   }
-  if (pops) std::memcpy(pops, host.data(), sizeof(double) * c->n);
+  if (pops) std::memcpy(pops, host, sizeof(double) * c->n);
   if (trace) *trace = tr;
   if (sink) *sink = host[c->n];
   if (!finite || !std::isfinite(host[c->n]) || !(tr > 0.0)) {
@@ -1375,12 +1373,11 @@ extern "C" qme_status qme_observe_weighted(const qme_ctx *c, const void *state,
   if (st != QME_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (c->elem == 8) e = launch_diag<double>(static_cast<const double *>(state), c->ld, c->n, c->diag, s);
-  else e = launch_diag<float>(static_cast<const float *>(state), c->ld, c->n, c->diag, s);
+  if (c->elem == 8) e = launch_diag<double>(static_cast<const double *>(state), c->ld, c->n, nullptr, c->diag, s);
+  else e = launch_diag<float>(static_cast<const float *>(state), c->ld, c->n, nullptr, c->diag, s);
   if (e != hipSuccess) { set_error(hipGetErrorString(e)); return QME_E_DEVICE; }
-  std::vector<double> pops(c->n);
-  HIP_OK(hipMemcpyAsync(pops.data(), c->diag, sizeof(double) * c->n, hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
+  const double *pops = c->diag;
   // the same FP64 sum, in index order, as the objective qme_adjoint returns
   double f = 0.0;
   for (int64_t u = 0; u < c->n; ++u) f += weights[u] * pops[u];
@@ -1606,6 +1603,7 @@ qme_ctx::~qme_ctx() {
   for (void *e : sel_ev)
     if (e) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
   if (sel_count_host) (void)hipHostFree(sel_count_host);
+  if (diag) (void)hipHostFree(diag);
   for (void *e : ev_start) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
   for (void *e : ev_stop) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
   for (void *p : {(void *)csr_ptr, (void *)csrt_ptr, (void *)kj_ptr, (void *)koff_ptr,
@@ -1614,7 +1612,7 @@ qme_ctx::~qme_ctx() {
                   (void *)csr_gamma, (void *)csr_channel, (void *)loff_row, (void *)loff_col,
                   (void *)loff_val})
     if (p) (void)hipFree(p);
-  for (void *p : {du_re, du_im, du_split, s_tables, (void *)parent_keep, (void *)d, (void *)leak, (void *)trw, (void *)diag, (void *)pi, (void *)cg,
+  for (void *p : {du_re, du_im, du_split, s_tables, (void *)parent_keep, (void *)d, (void *)leak, (void *)trw, (void *)pi, (void *)cg,
                   (void *)tau, (void *)ca, (void *)upi, (void *)uc, (void *)ada, (void *)arrival_of,
                   (void *)h_ptr, (void *)h_col, (void *)h_val, (void *)t_row, (void *)t_col,
                   (void *)t_val})

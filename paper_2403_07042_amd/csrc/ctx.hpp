@@ -54,7 +54,8 @@ struct qme_ctx {
   int32_t *s_col = nullptr, *s_off = nullptr, *s_at = nullptr;
   void *s_val = nullptr;                     // storage type
   double *s_phase = nullptr;                 // [n][2]
-  double *d = nullptr, *leak = nullptr, *diag = nullptr;
+  double *d = nullptr, *leak = nullptr;
+  double *diag = nullptr;   // pinned host memory: n populations and 8 scalars (qme_observe)
   double *trw = nullptr;              // trace weights (DissArgs::trw)
   int32_t *pi = nullptr;
   double *cg = nullptr;

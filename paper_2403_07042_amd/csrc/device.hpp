@@ -231,7 +231,8 @@ hipError_t launch_scalars_home(double *aux, hipStream_t s);
 template <typename T>
 hipError_t launch_dissipate(const DissArgs<T> &a, hipStream_t s);
 template <typename T>
-hipError_t launch_diag(const T *x_re, int64_t ld, int64_t n, double *out, hipStream_t s);
+hipError_t launch_diag(const T *x_re, int64_t ld, int64_t n, const double *aux, double *out,
+                       hipStream_t s);
 
 // Whole time steps of a system with n <= kSmallN in one single-workgroup
 // launch (state and dU held in LDS; see small.hip).  re / im / aux: the
