@@ -54,6 +54,18 @@ __device__ __forceinline__ double series_uniform(double x) {
   return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | unsigned(lo));
 }
 
+// __syncthreads with its wait for the wave's own LDS accesses spelt out.  The
+// compiler left that wait out at the head of the loop over the terms, whose
+// writes of v come at its end (ds_write, branch, s_barrier), so another wave
+// could read v before it was written: a few elements of a batch of 256 systems
+// differed in the last place between runs.
+__device__ __forceinline__ void series_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0); vmcnt and expcnt not waited for
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 template <typename T>
 __device__ __forceinline__ T series_fma(T a, T b, T c) {
   if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, b, c);
@@ -204,7 +216,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   }
 
   for (int k = a.order; k >= 1; --k) {
-    __syncthreads();
+    series_barrier();
 #pragma unroll
     for (int s = 0; s < S; ++s) {
 #pragma unroll
@@ -248,7 +260,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
       }
     }
     if (k == 1) break;
-    __syncthreads();
+    series_barrier();
     const T w = sgn * T(a.ratio[k]);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -320,13 +332,13 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   if constexpr (MODE == kSeriesFold || MODE == kSeriesStep) decohere();
   if constexpr (MODE == kSeriesStep) {
     fetch_first();
-    __syncthreads();   // every wave has read v
+    series_barrier();   // every wave has read v
     rotate();
     finish();
   }
   // (the row passes hand their results to LDS, by state, so that the rows are
   // written in order: the slots' order would leave parts of lines)
-  if constexpr (kRows) __syncthreads();
+  if constexpr (kRows) series_barrier();
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const int slot = (wave * S + s) * 64 + lane;
@@ -346,7 +358,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
     if constexpr (kRows) put(lds, int(c), w_re, w_im);
   }
   if constexpr (kRows) {
-    __syncthreads();
+    series_barrier();
     unit w_re[S], w_im[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
