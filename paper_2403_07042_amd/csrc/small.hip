@@ -365,38 +365,50 @@ template <typename T, int D, int G, int NT>
 __global__ __launch_bounds__(NT) void small_series_kernel(SmallArgs<T> p) {
   typedef T cplx __attribute__((ext_vector_type(2)));
   __shared__ cplx s_v[2][kSmallN * kSmallLd];
-  __shared__ int32_t s_state[64], s_slot[kSmallN];
+  __shared__ int32_t s_state[kSmallN], s_at[D][kSmallN];
+  __shared__ T s_k[D][kSmallN];
+  static_assert(D * kSmallN <= NT, "one entry per thread");
   const int n = p.n, tid = int(threadIdx.x), lane = tid & 63;
   const SmallSeries<T> &q = p.series;
   const int i = tid / n, j = tid - i * n;
   const bool in = i < n, low = in && j <= i;
   const int e = in ? i * kSmallLd + j : 0, ei = in ? i : 0, ej = in ? j : 0;
-  if (tid < n) {
-    s_state[tid] = q.slot_col[tid];
-    s_slot[q.slot_col[tid]] = tid;
+  // K's entries by state, through LDS (a thread's own reads of the tables cost
+  // a call of one step 1 to 4 us); every load is issued before the first wait
+  const int d0 = tid / kSmallN, slot = tid & (kSmallN - 1);
+  const bool has = d0 < D && d0 < q.entries && slot < n;
+  int32_t to = 0;
+  T k = T(0);
+  if (has) {
+    to = q.entry_at[d0 * 64 + slot] >> __builtin_ctz(unsigned(q.slot_bytes));
+    k = q.entry_val[d0 * 64 + slot];
   }
+  if (tid < n) s_state[tid] = q.slot_col[tid];
   cplx x = small_pair<T>(0, 0);
   if (in) x = small_pair<T>(p.re[i * p.ld + j], p.im[i * p.ld + j]);
+  const double aj = q.phase[2 * ej], bj = q.phase[2 * ej + 1], ai = q.phase[2 * ei],
+               bi = -q.phase[2 * ei + 1];
+  SmallElement<T, G> el;
+  el.load(p, ei, ej, lane);
+  SmallScalars sc{p.aux[0], p.aux[1], p.aux[2], p.aux[3], p.aux[4]};
+  __syncthreads();
+  if (d0 < D && slot < n) {
+    s_at[d0][s_state[slot]] = has ? s_state[to] : 0;
+    s_k[d0][s_state[slot]] = k;
+  }
   __syncthreads();
   // K's rows j and i as neighbours along this element's row and column
   int at1[D], at2[D];
   T k1[D], k2[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    const bool has = d < q.entries;
-    const int a = has ? d * 64 + s_slot[ej] : 0, b = has ? d * 64 + s_slot[ei] : 0;
-    at1[d] = ei * kSmallLd + s_state[q.entry_at[a] / q.slot_bytes];
-    at2[d] = s_state[q.entry_at[b] / q.slot_bytes] * kSmallLd + ej;
-    k1[d] = has ? q.entry_val[a] : T(0);
-    k2[d] = has ? q.entry_val[b] : T(0);
+    at1[d] = ei * kSmallLd + s_at[d][ej];
+    at2[d] = s_at[d][ei] * kSmallLd + ej;
+    k1[d] = s_k[d][ej];
+    k2[d] = s_k[d][ei];
   }
   // the phase left over by the two shifts: e^{i (shift_j - shift_i) dt} - 1
-  const double aj = q.phase[2 * ej], bj = q.phase[2 * ej + 1], ai = q.phase[2 * ei],
-               bi = -q.phase[2 * ei + 1];
   const double q_re = ai + aj + (ai * aj - bi * bj), q_im = bi + bj + (ai * bj + bi * aj);
-  SmallElement<T, G> el;
-  el.load(p, ei, ej, lane);
-  SmallScalars sc{p.aux[0], p.aux[1], p.aux[2], p.aux[3], p.aux[4]};
 
   int flip = 0;
   // v <- x + ... ; returns d with (e^{sgn i K dt} x) = x + d
@@ -490,13 +502,19 @@ hipError_t launch_small_steps(const SmallArgs<T> &a, hipStream_t s) {
     // up to eight entries in a row of dU: two sweeps over them against two per
     // term of the series (N = 32, three channels, FP64: 5.1 against 5.6 us per
     // step); else the series while H's rows have up to eight (N = 32 lattice
-    // 17.0 -> 2.7 us FP32, 16.6 -> 4.8 FP64; N = 12 2.4 -> 1.2 and 2.0)
+    // 17.0 -> 2.7 us FP32, 16.6 -> 4.8 FP64; N = 12 2.4 -> 1.2 and 2.0).  Of 17
+    // to 22 states the series takes both (N = 18 FP64, two leaks, a call of 1 /
+    // 100 steps: 13.2 / 335 us by the rows of dU, 6.0 / 267 by the series, 9.4 /
+    // 695 in the general kernel)
     hipError_t e;
-    if (a.n_gather <= 6 && a.row_max <= 8)
+    const bool series = a.n_gather <= 6 && a.series.order > 0 && a.series.entries <= 8;
+    if (a.n_gather <= 6 && a.row_max <= 8 && !(series && a.n > 16 && a.n <= 22))
       e = a.n <= 8 ? launch_small_rows<T, 64>(b, s)
-          : a.n <= 16 ? launch_small_rows<T, 256>(b, s) : launch_small_rows<T, 1024>(b, s);
-    else if (a.n_gather <= 6 && a.series.order > 0 && a.series.entries <= 8)
-      e = a.n <= 16 ? launch_small_series<T, 256>(b, s) : launch_small_series<T, 1024>(b, s);
+          : a.n <= 16 ? launch_small_rows<T, 256>(b, s)
+          : a.n <= 22 ? launch_small_rows<T, 512>(b, s) : launch_small_rows<T, 1024>(b, s);
+    else if (series)
+      e = a.n <= 16 ? launch_small_series<T, 256>(b, s)
+          : a.n <= 22 ? launch_small_series<T, 512>(b, s) : launch_small_series<T, 1024>(b, s);
     else
       e = launch_kernel(small_steps_kernel<T>, dim3(1), dim3(kSmallThreads), 0, s, b);
     if (e != hipSuccess) return e;

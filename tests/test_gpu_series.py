@@ -306,3 +306,16 @@ def test_single_workgroup_kernels_against_oracle(make, precision):
     _, trace, _ = sol.observe()
     sol.close()
     check((rho, got_sink, trace), (ref, sink), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("make", [
+    lambda: W.photon_lattice(16, 1, mu=0.1, gamma=0.05, dt=0.1, atoms_per_site=0, g=0.0),   # 256 threads
+    lambda: W.photon_lattice(22, 1, mu=0.1, gamma=0.05, dt=0.1, atoms_per_site=0, g=0.0),   # 512
+    lambda: W.photon_lattice(23, 1, mu=0.1, gamma=0.05, dt=0.1, atoms_per_site=0, g=0.0),   # 1024
+    lambda: W.jc_single(cap=8), lambda: W.jc_single(cap=11),       # N = 18: series; 24: rows of dU
+    # N = 20, |H dt| past the series: the rows of dU with 512 threads
+    lambda: dict(W.jc_single(cap=9), omega_c=[0.0], omega_a=[0.0], dt=60.0, g=[0.02]),
+])
+def test_single_workgroup_widths_against_oracle(make, precision):
+    test_single_workgroup_kernels_against_oracle(make, precision)
