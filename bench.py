@@ -5,22 +5,20 @@ Workload: 2D photon motion (Sec. IV.B) on a 32 x 32 lattice of cavities with
 one two-level atom each, single-excitation subspace (N = 2048), hopping
 mu = 0.01, coupling g = 0.01, photon leak 0.001 on the 124 boundary sites,
 dt = 0.01, photon started at site (16, 16).  One "step" is one full time step
-of the method: rho_u = U rho U^dag as two planar complex MFMA products (the
-first T = rho + dU rho, the second on the lower-triangle tiles only), the
-decoherence step, the FP64 symmetrisation, trace and sink, and the
-renormalisation.  Every boundary leak maps the single-excitation basis out of
-itself, so the decoherence step is one factor per element: it runs in the
-lower-triangle product's epilogue ("folded" steps), the one-workgroup FP64
-trace pass computes the renormalisation factor from the stored diagonal, and
-the next step's first product applies it.  Inputs are resident in HBM before
-the timed region starts.
+of the method: rho_u = U rho U^dag, the decoherence step, the trace and sink in
+FP64, and the renormalisation.  U is applied by its series (H has a few
+couplings per state, and the library picks that form by itself); every boundary
+leak maps the single-excitation basis out of itself, so the decoherence step is
+one factor per element and a step is one pass over the state.  Inputs are
+resident in HBM before the timed region starts.
 
 Prints one JSON line (rank 0, N = 1): value = FP32 time steps per second from
 a run with no profiling, plus the FP64 and split-BF16x3 rates, per-kernel
 durations from a second, profiled run of the same steps (every 8th step's
-kernels launched with start / stop events stamped by their own dispatch),
-the roofline entry of the dominant kernel (the first product) and the CPU
-oracle timed on the host cores.
+kernels launched with start / stop events stamped by their own dispatch; a
+profiled step runs its two passes), the roofline entry of the step's pass, the
+same steps with dense MFMA products (Solver.set_products(0)) with the matrix
+pipe's fraction in them, and the CPU oracle timed on the host cores.
 """
 from __future__ import annotations
 
@@ -134,13 +132,22 @@ def timed_leg(P, W, torch, wl, precision, steps, warmup, tiles="", tune=False):
     sol.step(steps)
     torch.cuda.synchronize()
     p1 = time.perf_counter()
-    prof = sol.profile_read()
+    kern = kernel_times(sol.profile_read())
+    # the same with dense products: rate, then kernel durations
+    few = min(steps, 200)
     sol.profile(False)
-    # per sampled step (one first product each): a kind launched on fewer
-    # steps (the folded steps' trace, once per call) counts at its share
-    sampled = max(prof["product_full"][1], 1)
-    kern = {k: (1e3 * ms / sampled) for k, (ms, cnt) in prof.items()}
+    sol.set_products(0)
+    sol.set_rho(rho0)
+    sol.step(min(warmup, 5))
+    dense_s = _timed(torch, lambda: sol.step(few))
+    sol.profile(PROFILE_EVERY)
+    sol.step(few)
+    torch.cuda.synchronize()
+    dense_kern = kernel_times(sol.profile_read())
+    sol.profile(False)
     out = {
+        "dense": {"steps": few, "steps_per_s": few / dense_s, "ms_per_step": 1e3 * dense_s / few,
+                  "kernels_us": dense_kern},
         "seconds": t1 - t0,
         "steps_per_s": steps / (t1 - t0),
         "ms_per_step": 1e3 * (t1 - t0) / steps,
@@ -152,9 +159,17 @@ def timed_leg(P, W, torch, wl, precision, steps, warmup, tiles="", tune=False):
         "tile2": sol.tile2,
         "tuned_split": None if tuned is None else bool(tuned[2]),
         "pops": pops, "trace": trace, "sink": sink, "n": sol.n, "ld": sol.ld,
+        "elem": sol.elem,
     }
     sol.close()
     return out
+
+
+def kernel_times(prof):
+    """us per sampled step (one first product or pass each): a kind launched on
+    fewer steps (the folded steps' trace, once per call) counts at its share."""
+    sampled = max(prof["product_full"][1], 1)
+    return {k: 1e3 * ms / sampled for k, (ms, cnt) in prof.items()}
 
 
 # Real flops the matrix cores execute per complex multiply-add: the FP32 and
@@ -170,15 +185,21 @@ def lower_flops(leg):
     return MFMA_FLOP_PER_CMAC * ld * t2 * t2 * t * (t + 1) / 2
 
 
+def state_bytes(leg):
+    """Bytes a step of one pass moves at least: both planes of the state in and
+    out, N x N elements each."""
+    return 4.0 * leg["elem"] * leg["n"] ** 2
+
+
 def executed_flops(leg):
-    """Flops one step executes on the matrix cores: the full product plus the
-    lower-triangle tiles."""
+    """Flops one step of dense products executes on the matrix cores: the full
+    product plus the lower-triangle tiles."""
     return MFMA_FLOP_PER_CMAC * leg["ld"] ** 3 + lower_flops(leg)
 
 
 def adjoint_leg(P, W, torch, wl, steps, every):
     """Wall time of one qme_adjoint call (forward with checkpoints, segment
-    recompute, three adjoint products per step, FP64 finalisation) for the
+    recompute, the adjoint steps, FP64 finalisation) for the
     centre photon population, per step; and the tied gradients it returns."""
     import numpy as np
     occ = P.basis(wl)
@@ -226,14 +247,6 @@ def batch_leg(P, W, torch, steps):
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     flops = sum(16.0 * s.n ** 3 for s in sols)
-    # what the matrix cores execute per batched step: both products of every
-    # instance in the 3M form (6 flop per complex multiply-add) over its padded
-    # ld, the lower product over its lower-triangle tiles
-    executed = 0.0
-    for s in sols:
-        t1_, t2_ = s.tiles
-        k = s.ld // t2_
-        executed += MFMA_FLOP_PER_CMAC * (s.ld ** 3 + s.ld * t2_ * t2_ * k * (k + 1) / 2)
     b.close()
     for s in sols:
         s.close()
@@ -241,11 +254,8 @@ def batch_leg(P, W, torch, steps):
     return {"instances": len(wls), "steps": steps, "batched_steps_per_s": rate,
             "tuned": {"use_graph": use_graph, "largest_first": largest,
                       "tiles_per_n": {str(n): list(t) for n, t in sorted(per_n.items())}},
-            "executed_tflops": executed * rate / 1e12,
-            "executed_frac_of_fp32_peak": executed * rate / 1e12 / PEAK_FP32_MFMA,
             "instance_steps_per_s": rate * len(wls), "ms_per_batched_step": 1e3 / rate,
-            "dense_equivalent_tflops": flops * rate / 1e12,
-            "dense_equivalent_frac_of_fp32_peak": flops * rate / 1e12 / PEAK_FP32_MFMA}
+            "dense_equivalent_tflops": flops * rate / 1e12}
 
 
 def _timed(torch, fn):
@@ -390,20 +400,21 @@ def plane_leg(P, W, torch, steps=100, warmup=5):
     durations (HIP events on the launch stream)."""
     wl = W.photon_plane(steps=steps)
     out = timed_leg(P, W, torch, wl, "fp32", steps, warmup)
-    flops = executed_flops(out)
+    dense = out["dense"]
+    dense["executed_frac_of_fp32_peak"] = (executed_flops(out) * dense["steps_per_s"] / 1e12
+                                           / PEAK_FP32_MFMA)
     return {"workload": "photon_plane_81x51_n4131", "precision": "fp32", "N": out["n"],
             "ld": out["ld"], "steps": steps, "steps_per_s": out["steps_per_s"],
             "ms_per_step": out["ms_per_step"], "kernels_us": out["kernels_us"],
-            "executed_tflops": flops * out["steps_per_s"] / 1e12,
-            "executed_frac_of_fp32_peak": flops * out["steps_per_s"] / 1e12 / PEAK_FP32_MFMA}
+            "state_tb_s": state_bytes(out) / (out["ms_per_step"] * 1e-3) / 1e12,
+            "dense_products": dense}
 
 
 def pure_leg(P, W, torch, steps=2000, warmup=20):
-    """The same plane as a pure state (qme_pure_step: psi <- U psi / |psi|,
-    one launch per step), FP32 and FP64: steps/s from HIP events on the
-    launch stream, and the dU bytes each step streams (algorithmic: 2 planes
-    of N x N, the padding columns of each row excluded) against the HBM
-    peak.  The final states are kept (key "_psi") for the parity check of the
+    """The same plane as a pure state (qme_pure_step: psi <- U psi / |psi|, the
+    steps of a call in one launch, the vector and H's rows held on one compute
+    unit), FP32 and FP64: steps/s, and us per step from HIP events on the
+    launch stream.  The final states are kept (key "_psi") for the parity check of the
     CPU-baseline leg."""
     wl = W.photon_plane()
     occ = P.basis(wl)
@@ -424,11 +435,7 @@ def pure_leg(P, W, torch, steps=2000, warmup=20):
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         us = 1e3 * e0.elapsed_time(e1) / steps
-        per_step = 2.0 * sol.elem * sol.n * sol.n
         out[prec] = {"steps_per_s": steps / wall, "us_per_step": us,
-                     "du_bytes_per_step": per_step,
-                     "achieved_tb_s": per_step / (us * 1e-6) / 1e12,
-                     "frac_of_hbm_peak": per_step / (us * 1e-6) / 1e9 / PEAK_HBM,
                      "_psi": (sol.get_psi(), site, wl)}
         sol.close()
     return out
@@ -584,31 +591,43 @@ def main():
     main_leg = res.get("fp32") or res.get("fp64")
     prec = "fp32" if "fp32" in res else "fp64"
     peak = PEAK_FP32_MFMA if prec == "fp32" else PEAK_FP64_MFMA
-    avg_us = main_leg["kernels_us"]["product_full"]
+    dense = main_leg["dense"]
+    avg_us = dense["kernels_us"]["product_full"]
     ld = main_leg["ld"]
-    # the first product executes 3 real ld^3 products (Gauss's 3M form), 6 ld^3 flop
+    # the step: one pass over the state (one launch per step)
+    tb_s = state_bytes(main_leg) / (main_leg["ms_per_step"] * 1e-3) / 1e12
+    roofline = {"bound": "hbm",
+                "kernel": "series_pass_kernel (both rotations of a step's rows and the "
+                          "decoherence factor, one launch per step)",
+                "achieved": tb_s, "peak": PEAK_HBM / 1e3, "unit": "TB/s",
+                "frac": tb_s / (PEAK_HBM / 1e3),
+                "traffic": None,
+                "per_launch_bytes": state_bytes(main_leg),
+                "per_launch_basis": "both N x N planes of the state read and written once",
+                "avg_launch_us": 1e3 * main_leg["ms_per_step"],
+                "duration_source": "wall time per step of the throughput pass (one launch per "
+                                   "step, back to back)"}
+    # the first dense product executes 3 real ld^3 products (Gauss's 3M form), 6 ld^3 flop
     executed_per_launch = MFMA_FLOP_PER_CMAC * ld ** 3
     achieved = executed_per_launch / (avg_us * 1e-6) / 1e12
-    roofline = {"bound": "mfma",
-                "kernel": f"cgemm_{prec}_kernel<{main_leg['tile1']}, conj_b> "
-                          "(first product T = rho + dU rho, full tiles)",
-                "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                "frac": achieved / peak,
-                "traffic": measured_traffic() if prec == "fp32" else None,
-                "per_launch_flop": executed_per_launch,
-                "per_launch_basis": "three real ld x ld x ld products (3M form of the complex "
-                                    f"product), 6*ld^3 flop, ld = {ld}; equal to the MFMA "
-                                    "operations the counters read per launch",
-                "avg_launch_us": avg_us,
-                "duration_source": "HIP start / stop events stamped by the kernel's own "
-                                   "dispatch, every 8th step of a profiled pass of the same "
-                                   "steps (the throughput pass runs without events)",
-                "zgemm_equivalent_tflops": 8.0 * n ** 3 / (avg_us * 1e-6) / 1e12,
-                "zgemm_equivalent_note": "8*N^3 (four-real-product convention) over the same "
-                                         "duration; not a roofline fraction",
-                "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, "
-                                "copy-calibrated; " + TRAFFIC_FP32_PRODUCT["source"] + ")",
-                "operand_bytes_per_launch": 24.0 * n * n}
+    dense["executed_frac_of_peak"] = executed_flops(main_leg) * dense["steps_per_s"] / 1e12 / peak
+    dense["lower_product_frac_of_peak"] = (lower_flops(main_leg)
+                                           / (dense["kernels_us"]["product_lower"] * 1e-6)
+                                           / 1e12 / peak)
+    dense["roofline"] = {
+        "bound": "mfma",
+        "kernel": f"cgemm_{prec}_kernel<{main_leg['tile1']}, conj_b> "
+                  "(first product T = rho + dU rho, full tiles)",
+        "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
+        "traffic": measured_traffic() if prec == "fp32" else None,
+        "per_launch_flop": executed_per_launch,
+        "per_launch_basis": "three real ld x ld x ld products (3M form of the complex "
+                            f"product), 6*ld^3 flop, ld = {ld}",
+        "avg_launch_us": avg_us,
+        "duration_source": "HIP start / stop events stamped by the kernel's own dispatch, "
+                           "every 8th step of a profiled pass",
+        "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, "
+                        "copy-calibrated; " + TRAFFIC_FP32_PRODUCT["source"] + ")"}
 
     cpu, parity = None, None
     if args.cpu_steps > 0:
@@ -637,14 +656,11 @@ def main():
                    "ld": main_leg["ld"], "dt": 0.01, "mu": 0.01, "g": 0.01,
                    "boundary_leak": 0.001, "precision": prec},
         "dense_equivalent_tflops": flops_step * main_leg["steps_per_s"] / 1e12,
-        "executed_tflops": executed_flops(main_leg) * main_leg["steps_per_s"] / 1e12,
-        "executed_frac_of_peak": executed_flops(main_leg) * main_leg["steps_per_s"] / 1e12 / peak,
-        "lower_product_frac_of_peak": lower_flops(main_leg) / (main_leg["kernels_us"]["product_lower"]
-                                                               * 1e-6) / 1e12 / peak,
         "kernels_us": main_leg["kernels_us"],
         "kernels_us_sum": main_leg["kernels_us_sum"],
         "profiled_ms_per_step": main_leg["profiled_ms_per_step"],
         "roofline": roofline,
+        "dense_products": dense,
         "cpu_baseline": cpu,
         "parity": parity,
         "adjoint_ms_per_step": adj["ms_per_step"] if adj else None,
@@ -661,23 +677,25 @@ def main():
         b = res["bf16x3"]
         line["bf16x3"] = {"steps_per_s": b["steps_per_s"], "ms_per_step": b["ms_per_step"],
                           "steps": args.bf16x3_steps, "kernels_us": b["kernels_us"],
-                          "dense_equivalent_frac_of_fp32_peak":
-                              flops_step * b["steps_per_s"] / 1e12 / PEAK_FP32_MFMA,
                           "tiles": [b["tile1"], b["tile2"]],
+                          "dense_products": b["dense"],
                           "bf16_mfma_tflops_first_product":
-                              6 * flops_product / (b["kernels_us"]["product_full"] * 1e-6) / 1e12,
+                              6 * flops_product / (b["dense"]["kernels_us"]["product_full"] * 1e-6)
+                              / 1e12,
                           "first_product_frac_of_bf16_peak":
-                              6 * flops_product / (b["kernels_us"]["product_full"] * 1e-6) / 1e12
-                              / PEAK_BF16_MFMA}
+                              6 * flops_product / (b["dense"]["kernels_us"]["product_full"] * 1e-6)
+                              / 1e12 / PEAK_BF16_MFMA}
     if "fp64" in res:
         f = res["fp64"]
         line["fp64"] = {"steps_per_s": f["steps_per_s"], "ms_per_step": f["ms_per_step"],
                         "steps": args.fp64_steps, "kernels_us": f["kernels_us"],
-                        "executed_frac_of_fp64_peak":
-                            executed_flops(f) * f["steps_per_s"] / 1e12 / PEAK_FP64_MFMA,
-                        "lower_product_frac_of_fp64_peak":
-                            lower_flops(f) / (f["kernels_us"]["product_lower"] * 1e-6) / 1e12
-                            / PEAK_FP64_MFMA}
+                        "state_tb_s": state_bytes(f) / (f["ms_per_step"] * 1e-3) / 1e12,
+                        "dense_products": f["dense"],
+                        "dense_executed_frac_of_fp64_peak":
+                            executed_flops(f) * f["dense"]["steps_per_s"] / 1e12 / PEAK_FP64_MFMA,
+                        "dense_lower_product_frac_of_fp64_peak":
+                            lower_flops(f) / (f["dense"]["kernels_us"]["product_lower"] * 1e-6)
+                            / 1e12 / PEAK_FP64_MFMA}
         if "fp32" in res:
             line["fp32_speedup_over_fp64"] = res["fp32"]["steps_per_s"] / f["steps_per_s"]
     print(json.dumps(line), flush=True)
