@@ -428,7 +428,8 @@ qme_status qme_pure_get(const qme_ctx *ctx, const void *state_dev, int32_t n_vec
 /* Advance every vector by n_steps steps psi <- (psi + dU psi) / |psi|, with
  * dU = U - I the context's propagator and |psi| summed in FP64 from the
  * stored vector; the stored result is U applied to a unit vector.  One
- * launch per step.  state_dev and workspace_dev (qme_pure_layout bytes)
+ * launch per step, or where H's series is used (qme_set_products) one for all
+ * steps of the call.  state_dev and workspace_dev (qme_pure_layout bytes)
  * are 256-byte aligned and do not overlap.  QME_E_STATE when a decoherence
  * operator acts on the basis (the state would not stay pure).
  * Asynchronous on hip_stream. */
@@ -444,7 +445,8 @@ typedef struct qme_batch qme_batch;
  * Bind `count` FP32 contexts and their device state buffers (one each,
  * layouts from qme_state_layout, 256-byte aligned) into a batch.  Each step
  * of the batch is one launch per phase (first product, lower-triangle
- * product, trace/sink pass, decoherence pass) covering the tiles of every
+ * product, trace/sink pass, decoherence pass; the first two once more for
+ * instances that step by the series) covering the tiles of every
  * instance, largest instances first; a run of n steps is captured once into
  * a hipGraph and replayed.  Each instance's two products run in the tile
  * edges of its context (qme_set_tiles; 32 or 64, else QME_E_UNSUPPORTED),
@@ -541,8 +543,8 @@ qme_status qme_set_split(qme_ctx *ctx, int32_t enable);
 
 /* Single-workgroup path (on by default): for FP32 and FP64 contexts with
  * N <= 32, qme_step runs all its steps in one launch of one workgroup per
- * 4096 steps, the state and dU held in LDS.  The arithmetic is the same step;
- * the products accumulate with scalar FMAs in k order instead of MFMA, so
+ * 4096 steps, the state and dU (or H's entries, for U by its series) held in
+ * LDS and registers.  The arithmetic is the same step with scalar FMAs, so
  * results differ from the tiled path by rounding only.  With profiling on,
  * such a launch is counted under index 0 of qme_profile_read.  enable: 0 or
  * 1, else QME_E_ARG. */
