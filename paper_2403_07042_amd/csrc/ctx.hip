@@ -683,7 +683,9 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
       // several launches per step)
       if (n > kSmallN) {
         c->series_order = sp.order;
-        c->series_faster = sp.faster;
+        const bool folded = c->jt.n_gather == 0 && c->jt.n_csr == 0;
+        c->series_faster = sp.faster && series_step_us(sp, n, int(c->elem), folded, c->cus) <
+                                            dense_step_us(c->precision, n);
       } else {
         c->small_order = sp.order;
         c->small_entries = sp.slice_off[1];

@@ -168,6 +168,13 @@ hipError_t step_once(qme_ctx *c, const void *in, void *out, void *y, void *z, hi
 // Whether the steps apply the propagator by its series (series_tile.hpp) or
 // multiply by the dense dU.
 bool uses_series(const qme_ctx *c);
+// Expected time of a step of a density matrix by the series or by dense
+// products, in us; folded: no decoherence pass (series.hip).
+double series_step_us(const SeriesPlan &p, int64_t n, int elem, bool folded, int cus);
+double dense_step_us(int precision, int64_t n);
+// Times us[i] measured at at[i], between them in proportion of the logarithms,
+// past the last growing with the given power of n.
+double interpolate_us(const double *at, const double *us, int count, double power, double n);
 // A row pass of the context's series (sign 1: conj(U), -1: U); phase: with the
 // whole phase of the propagator (a step of a density matrix needs only the
 // phase between components).

@@ -854,12 +854,13 @@ SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
   p.order = int(p.coef.size()) - 1;
   size_t nnz = 0;
   for (const auto &row : rows) nnz += row.size();
-  // A step's series costs order (entries per row + 3) LDS accesses per element,
-  // its dense products N multiply-adds.  Measured (MI355X, us per step, series
-  // against dense): N = 2048 lattice (cost 18) 44 / 611 FP32 and 95 / 1296
-  // FP64, N = 144 TCH (25) 16.1 / 20.6, N = 64 TCH (18) 13.4 / 14.2, but N = 64
-  // hydrogen bond (43) 16.5 / 15.5 and N = 48 (54) 19.0 / 16.4.  N <= 32 has
-  // the single-workgroup path.
+  // A step's series costs about order (entries per row + 3) LDS accesses per
+  // element, its dense products N multiply-adds.  This line is that of the
+  // small, launch-bound systems (MI355X, us per step, series against dense): N =
+  // 144 TCH (cost 25) 16.1 / 20.6, N = 64 TCH (18) 13.4 / 14.2, but N = 64
+  // hydrogen bond (43) 16.5 / 15.5 and N = 48 (54) 19.0 / 16.4.  It counts mean
+  // rows, so it does not see long rows of a few states or what long rows cost at
+  // large N: series_step_us decides those.  N <= 32 has the single-workgroup path.
   const double cost = double(p.order) * (double(nnz) / double(std::max<int64_t>(n, 1)) + 3.0);
   p.ok = p.order >= 1 && cost < 2.0 * double(n);
   p.faster = p.ok && cost < 0.6 * double(n);
@@ -906,6 +907,10 @@ SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
       }
     p.slice_off.push_back(p.slice_off.back() + int32_t(longest));
   }
+  size_t apart = 0;
+  for (size_t e = 0; e + 1 < p.slot.size(); ++e)
+    apart += e % 64 != 63 && p.slot[e + 1] != p.slot[e] + 1;
+  p.scattered = double(apart) / double(std::max<size_t>(p.slot.size(), 1));
   // (a pass loads the first few entries of a slice whatever their number)
   p.slot.resize(p.slot.size() + 8 * 64, 0);
   p.val.resize(p.val.size() + 8 * 64, 0.0);

@@ -164,7 +164,7 @@ bool propagator_increment(const Model &m, const Csr &h, std::vector<double> &re,
 // 64 (sliced ELL); a shorter row is filled with zero entries on its own slot.
 struct SeriesPlan {
   bool ok = false;                  // the plan exists (H sparse, |K dt| <= 1)
-  bool faster = false;              // and its passes are expected to beat the dense products
+  bool faster = false;              // and H is sparse enough for the default (series_faster)
   int order = 0;
   double theta = 0.0;               // |K dt|_1
   std::vector<double> coef;         // e^z = sum_k coef[k] z^k, k <= order
@@ -173,6 +173,7 @@ struct SeriesPlan {
   std::vector<int32_t> slice_off;   // per slice of 64 slots
   std::vector<int32_t> slot;        // per entry (slice, entry, lane): the neighbour's slot
   std::vector<double> val;
+  double scattered = 0.0;           // share of the entries whose neighbour does not follow the lane before's
   std::vector<double> phase_re, phase_im;   // e^{i shift dt} - 1 per state
 };
 constexpr int kMaxSeriesOrder = 24;

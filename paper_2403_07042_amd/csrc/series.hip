@@ -2,6 +2,9 @@
 #include "series_tile.hpp"
 
 #include <algorithm>
+#include <cmath>
+
+#include "ctx.hpp"
 
 namespace qme {
 
@@ -128,6 +131,68 @@ static SeriesShape series_shape(int64_t n) {
 
 int series_slot_bytes(int64_t n) { return std::min(series_shape(n).bytes, 16); }
 int series_slices_per_wave(int64_t n) { return series_shape(n).slices; }
+
+// A step is as slow as the longest wave of a workgroup, or as the workgroup's
+// LDS reads where all its rows are long, times the rounds of workgroups on the
+// device: not as the mean row of H.  The figures are fits to steps timed on the
+// MI355X with rows of 2 to 400 entries and with a star (one state coupled to all
+// others) at N = 40 ... 8190, in FP32 and FP64 (order 8 and 12); of 380 pairs of
+// times six choices cost more than 5% against the better form (at most 28%).
+// Entries: a wave takes them C at a time, the first C of a slice (of the shapes
+// with one or two slices) from registers, each further C after a load that is
+// waited for (0.42 us FP32, 0.31 FP64; four slices and more in FP64 0.5, eight
+// 0.8).  Series / dense, us per step: star N = 65 103 / 14, 501 805 / 36, 2048
+// 3463 / 615; rows of 64 at N = 513 217 / 43, 1025 260 / 144, 2048 407 / 643,
+// 4096 1823 / 4717; rows of 128 at N = 2048 852 / 646; of 200 at 4096 6797 / 4740.
+// LDS: 128 bytes per clock, half as much again where lanes read scattered states
+// (bank conflicts: random rows of 32 at N = 2048 371 against 201).
+double series_step_us(const SeriesPlan &p, int64_t n, int elem, bool folded, int cus) {
+  const SeriesShape f = series_shape(n);
+  const int c = elem == 4 ? 4 : 3;
+  const double load = f.slices == 8 ? 0.8 : elem == 4 ? 0.42 : f.slices <= 2 ? 0.31 : 0.5;
+  const int64_t slices = int64_t(p.slice_off.size()) - 1;
+  double longest = 0.0;
+  for (int64_t q0 = 0; q0 < slices; q0 += f.slices) {
+    double wave = 0.0;
+    for (int64_t q = q0; q < std::min(slices, q0 + f.slices); ++q) {
+      const int len = p.slice_off[size_t(q) + 1] - p.slice_off[size_t(q)];
+      const double kept = f.slices <= 2 && len > 0 ? 1.0 : 0.0;
+      wave += 0.15 * kept + load * std::max(0.0, double(len) / c - kept);
+    }
+    longest = std::max(longest, wave);
+  }
+  // workgroups that a compute unit holds (LDS, 1024 threads at four waves per
+  // SIMD), and the rounds that the row groups need
+  const int per_cu = std::min(163840 / (2 * f.slices * f.threads * f.bytes), 1024 / f.threads);
+  const int64_t groups = (n * elem + f.bytes - 1) / f.bytes, room = int64_t(cus) * per_cu;
+  const double rounds = double((groups + room - 1) / room);
+  const double resident = double(std::min<int64_t>(per_cu, (groups + cus - 1) / cus));
+  const double lds = resident * double(p.slice_off.back()) * 64.0 * 2.0 * f.bytes / (137.0 * 2400.0) *
+                     (1.0 + 0.55 * p.scattered);
+  const double term = (f.threads == 1024 ? 1.8 : elem == 4 ? 0.4 : 0.3) + std::max(longest, lds);
+  const double move = 4.0 * double(n) * double(n) * elem / 5e6;   // the planes in and out, 5 TB/s
+  return rounds * 2.0 * p.order * term + move + 2.0 + (folded ? 0.0 : 6.0 + move);
+}
+
+// Measured steps by dense products (MI355X, us per step; the launches' latency
+// up to N = 256, the matrix cores from N = 1024), between them in proportion of
+// the logarithms.
+double dense_step_us(int precision, int64_t n) {
+  static constexpr double kN[7] = {64, 128, 256, 512, 1024, 2048, 4096};
+  static constexpr double kFp64[7] = {21, 22.5, 30, 68, 245, 1310, 10500};
+  static constexpr double kFp32[7] = {14, 17, 26, 43, 140, 620, 4650};
+  static constexpr double kBf16x3[7] = {23, 24.5, 29, 42, 150, 420, 4050};
+  const double *us = precision == QME_FP64 ? kFp64 : precision == QME_FP32 ? kFp32 : kBf16x3;
+  return interpolate_us(kN, us, 7, 3.0, double(n));
+}
+
+double interpolate_us(const double *at, const double *us, int count, double power, double n) {
+  if (n <= at[0]) return us[0];
+  for (int i = 1; i < count; ++i)
+    if (n <= at[i])
+      return us[i - 1] * std::pow(us[i] / us[i - 1], std::log(n / at[i - 1]) / std::log(at[i] / at[i - 1]));
+  return us[count - 1] * std::pow(n / at[count - 1], power);
+}
 
 template <typename T>
 hipError_t launch_series_pass(const SeriesArgs<T> &a, int mode, hipStream_t s) {

@@ -1,0 +1,70 @@
+"""Which form of the propagator the steps take by default (qme_set_products -1):
+never the series where H has rows so long that its passes are the slower form,
+on both sides of the line.  The forms round differently, so a state tells which
+one ran."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+P = pytest.importorskip("paper_2403_07042_amd")
+
+
+def general(n, rows, cols, dt=0.3, row_sum=1.0):
+    """A closed general model: couplings of one value, |H|_1 = row_sum."""
+    r, c = np.concatenate([rows, cols]), np.concatenate([cols, rows])
+    longest = np.bincount(r, minlength=n).max()
+    return {"general": True, "name": f"general_{n}", "n": n, "jumps": [], "dt": dt,
+            "h": (r.astype(np.int32), c.astype(np.int32), np.full(r.size, row_sum / longest))}
+
+
+def star(n):
+    """State 0 coupled to all others (one cavity with many atoms, one excitation)."""
+    return general(n, np.zeros(n - 1, int), np.arange(1, n))
+
+
+def ring(n, degree):
+    """Every state coupled to its degree / 2 next and to as many before."""
+    i = np.arange(n)
+    return general(n, np.tile(i, degree // 2), np.concatenate([(i + k) % n for k in range(1, degree // 2 + 1)]))
+
+
+def tavis_cummings(atoms):
+    """One cavity with `atoms` atoms and at most one excitation: the photon's
+    state is coupled to every atom's."""
+    return {"name": f"tc_{atoms}", "atoms": [atoms], "photon_cap": [1], "exc_min": 0, "exc_max": 1,
+            "omega_c": [1.0], "omega_a": [1.0] * atoms, "g": [0.05] * atoms, "hops": [],
+            "jumps": [(W.PHOTON_LEAK, 0, -1, 0.01)], "dt": 0.05}
+
+
+def states(wl, precision, forms):
+    sol = P.Solver(wl, precision)
+    psi = W.haar_psi(sol.n, 3)
+    rho0 = np.outer(psi, psi.conj())
+    out = []
+    for form in forms:
+        print(f"{wl['name']} N={sol.n} {precision} form={form}", flush=True)
+        sol.set_products(form)
+        sol.set_rho(rho0)
+        sol.step(2)
+        out.append(sol.get_rho()[0])
+    sol.close()
+    return out
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64", "bf16x3"])
+@pytest.mark.parametrize("make", [lambda: star(129), lambda: star(501), lambda: star(2048),
+                                  lambda: tavis_cummings(64), lambda: ring(513, 32), lambda: ring(2048, 128)])
+def test_long_rows_take_dense_products(make, precision):
+    default, dense = states(make(), precision, (-1, 0))
+    assert np.array_equal(default, dense)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64", "bf16x3"])
+@pytest.mark.parametrize("make", [lambda: ring(129, 2), lambda: ring(513, 4), lambda: ring(2048, 16)])
+def test_short_rows_take_the_series(make, precision):
+    default, dense, series = states(make(), precision, (-1, 0, 1))
+    assert np.array_equal(default, series) and not np.array_equal(default, dense)
