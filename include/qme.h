@@ -428,11 +428,11 @@ qme_status qme_pure_get(const qme_ctx *ctx, const void *state_dev, int32_t n_vec
 /* Advance every vector by n_steps steps psi <- (psi + dU psi) / |psi|, with
  * dU = U - I the context's propagator and |psi| summed in FP64 from the
  * stored vector; the stored result is U applied to a unit vector.  One
- * launch per step, or where H's series is used (qme_set_products) one for all
- * steps of the call.  state_dev and workspace_dev (qme_pure_layout bytes)
- * are 256-byte aligned and do not overlap.  QME_E_STATE when a decoherence
- * operator acts on the basis (the state would not stay pure).
- * Asynchronous on hip_stream. */
+ * launch per step, or where H's series is used (qme_set_products; by default a
+ * rule of its own on H's rows) one for all steps of the call.  state_dev and
+ * workspace_dev (qme_pure_layout bytes) are 256-byte aligned and do not
+ * overlap.  QME_E_STATE when a decoherence operator acts on the basis (the
+ * state would not stay pure).  Asynchronous on hip_stream. */
 qme_status qme_pure_step(qme_ctx *ctx, void *state_dev, int32_t n_vec, int64_t n_steps,
                          void *workspace_dev, void *hip_stream);
 

@@ -686,6 +686,7 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
         const bool folded = c->jt.n_gather == 0 && c->jt.n_csr == 0;
         c->series_faster = sp.faster && series_step_us(sp, n, int(c->elem), folded, c->cus) <
                                             dense_step_us(c->precision, n);
+        c->pure_series_faster = pure_series_us(sp, n, int(c->elem)) < pure_dense_us(n, int(c->elem));
       } else {
         c->small_order = sp.order;
         c->small_entries = sp.slice_off[1];

@@ -48,6 +48,7 @@ struct qme_ctx {
   int series_order = 0;
   int small_order = 0, small_entries = 0;    // n <= kSmallN: SmallSeries
   bool series_faster = false;                // than the dense products (the default's choice)
+  bool pure_series_faster = false;           // the same for pure states
   double series_ratio[qme::kSeriesMaxOrder + 1] = {};
   bool series_phase = false;                 // the components' shifts differ
   void *s_tables = nullptr;                  // owns the tables of the series:
@@ -172,6 +173,9 @@ bool uses_series(const qme_ctx *c);
 // products, in us; folded: no decoherence pass (series.hip).
 double series_step_us(const SeriesPlan &p, int64_t n, int elem, bool folded, int cus);
 double dense_step_us(int precision, int64_t n);
+// The same for a step of a pure state (pure.hip).
+double pure_series_us(const SeriesPlan &p, int64_t n, int elem);
+double pure_dense_us(int64_t n, int elem);
 // Times us[i] measured at at[i], between them in proportion of the logarithms,
 // past the last growing with the given power of n.
 double interpolate_us(const double *at, const double *us, int count, double power, double n);

@@ -860,7 +860,8 @@ SeriesPlan plan_series(const Csr &h, double dt, bool fp64, int per_wave) {
   // 144 TCH (cost 25) 16.1 / 20.6, N = 64 TCH (18) 13.4 / 14.2, but N = 64
   // hydrogen bond (43) 16.5 / 15.5 and N = 48 (54) 19.0 / 16.4.  It counts mean
   // rows, so it does not see long rows of a few states or what long rows cost at
-  // large N: series_step_us decides those.  N <= 32 has the single-workgroup path.
+  // large N: series_step_us and, for pure states, pure_series_us decide those.  N <=
+  // 32 has the single-workgroup path.
   const double cost = double(p.order) * (double(nnz) / double(std::max<int64_t>(n, 1)) + 3.0);
   p.ok = p.order >= 1 && cost < 2.0 * double(n);
   p.faster = p.ok && cost < 0.6 * double(n);

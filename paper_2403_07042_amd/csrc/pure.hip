@@ -336,18 +336,73 @@ static hipError_t launch_series_shape(const PureSeriesArgs<T> &a, int nv, hipStr
 
 // The registers that a lane can give its rows' entries (128 at four waves per
 // SIMD) set C: rows with more entries read the rest from memory in each term.
+struct PureShape {
+  int slices, kept, threads;   // S, C, NT
+};
+static constexpr PureShape pure_shape(int64_t n, bool fp32) {
+  if (n <= 256) return {1, fp32 ? 12 : 8, 256};
+  if (n <= 1024) return {1, fp32 ? 12 : 8, 1024};
+  if (n <= 2048) return {2, fp32 ? 12 : 6, 1024};
+  if (n <= 3072) return {3, fp32 ? 8 : 4, 1024};
+  if (n <= 4096) return {4, fp32 ? 6 : 4, 1024};
+  if (n <= 5120) return {5, fp32 ? 4 : 3, 1024};
+  return {8, 2, 1024};
+}
+
+// A step is a chain of `order` terms on one compute unit, each as long as the
+// wave with the most entries past those in registers: they are read one after
+// another, 0.18 us each from the L2, 0.38 where they no longer fit it (4 MB).  The
+// dense step streams dU through the whole device, or is one launch.  Fits to steps
+// timed with rows of 2 to 400 entries and a star at N = 40 ... 4097; series /
+// dense, us per step: rows of 2 at N = 513 FP32 2.8 / 3.9, of 8 at 2048 5.4 / 5.5
+// (scattered 8.9 / 5.6), of 32 at 2048 64 / 5.5 and 4096 169 / 21.6, of 200 at 4096
+// 2726 / 21.6; star N = 65 50 / 3.6, 2048 2564 / 5.8; FP64 rows of 4 at 4096 14.5 /
+// 39.9, of 8 at 1025 12.7 / 5.4.
+double pure_series_us(const SeriesPlan &p, int64_t n, int elem) {
+  const PureShape f = pure_shape(n, elem == 4);
+  const int64_t slices = int64_t(p.slice_off.size()) - 1;
+  int64_t longest = 0, more = 0, kept = 0;
+  for (int64_t q0 = 0; q0 < slices; q0 += f.slices) {
+    int64_t wave = 0;
+    for (int64_t q = q0; q < std::min(slices, q0 + f.slices); ++q) {
+      const int64_t len = p.slice_off[size_t(q) + 1] - p.slice_off[size_t(q)];
+      wave += std::max<int64_t>(0, len - f.kept);
+      kept += std::min<int64_t>(len, f.kept);
+    }
+    more += wave;
+    longest = std::max(longest, wave);
+  }
+  const bool in_l2 = more * 64 * (4 + elem) <= 4 << 20;
+  const double lds = double(kept) * 64.0 * 2.0 * elem / (128.0 * 2400.0) * (0.55 + 0.95 * p.scattered);
+  const double latency = f.threads == 256 ? 0.23 : 0.2 + 0.1 * f.slices + (elem == 8 && f.slices >= 4 ? 0.2 : 0.0);
+  return p.order * (latency + lds + (in_l2 ? 0.18 : 0.38) * double(longest));
+}
+
+// Measured (MI355X, us per step in calls of 20).
+double pure_dense_us(int64_t n, int elem) {
+  static constexpr double kN[6] = {64, 256, 512, 1024, 2048, 4096};
+  static constexpr double kFp32[6] = {3.1, 3.3, 3.7, 4.5, 5.6, 21.5};
+  static constexpr double kFp64[6] = {3.0, 3.4, 3.9, 5.1, 11.7, 40.0};
+  return interpolate_us(kN, elem == 4 ? kFp32 : kFp64, 6, 2.0, double(n));
+}
+
 template <typename T>
 static hipError_t launch_pure_series(const PureSeriesArgs<T> &a, int nv, hipStream_t s) {
   constexpr bool F = sizeof(T) == 4;
   if (a.n < 1 || a.n > kSeriesMaxN || a.order < 1 || a.order > kSeriesMaxOrder || nv < 1)
     return hipErrorInvalidValue;
-  if (a.n <= 256) return launch_series_shape<T, 1, F ? 12 : 8, 256>(a, nv, s);
-  if (a.n <= 1024) return launch_series_shape<T, 1, F ? 12 : 8, 1024>(a, nv, s);
-  if (a.n <= 2048) return launch_series_shape<T, 2, F ? 12 : 6, 1024>(a, nv, s);
-  if (a.n <= 3072) return launch_series_shape<T, 3, F ? 8 : 4, 1024>(a, nv, s);
-  if (a.n <= 4096) return launch_series_shape<T, 4, F ? 6 : 4, 1024>(a, nv, s);
-  if (a.n <= 5120) return launch_series_shape<T, 5, F ? 4 : 3, 1024>(a, nv, s);
-  return launch_series_shape<T, 8, 2, 1024>(a, nv, s);
+  // the shape that pure_shape gives for the largest N of each line
+  auto run = [&](auto top) {
+    constexpr PureShape f = pure_shape(decltype(top)::value, F);
+    return launch_series_shape<T, f.slices, f.kept, f.threads>(a, nv, s);
+  };
+  if (a.n <= 256) return run(std::integral_constant<int64_t, 256>{});
+  if (a.n <= 1024) return run(std::integral_constant<int64_t, 1024>{});
+  if (a.n <= 2048) return run(std::integral_constant<int64_t, 2048>{});
+  if (a.n <= 3072) return run(std::integral_constant<int64_t, 3072>{});
+  if (a.n <= 4096) return run(std::integral_constant<int64_t, 4096>{});
+  if (a.n <= 5120) return run(std::integral_constant<int64_t, 5120>{});
+  return run(std::integral_constant<int64_t, kSeriesMaxN>{});
 }
 
 template <typename T, int NV>
@@ -424,7 +479,7 @@ qme_status pure_run(qme_ctx *c, void *state, int32_t n_vec, int64_t n_steps, voi
                     hipStream_t s) {
   const size_t plane = size_t(n_vec) * size_t(c->ld);
   T *a = static_cast<T *>(state), *b = static_cast<T *>(ws);
-  if (c->series_order > 0 && c->products != 0) {
+  if (c->series_order > 0 && (c->products == 1 || (c->products < 0 && c->pure_series_faster))) {
     PureSeriesArgs<T> p{a, a + plane, c->ld, int32_t(c->n), c->series_order,
                         series_slot_bytes(c->n), c->s_col, c->s_off, c->s_at,
                         static_cast<const T *>(c->s_val), c->s_phase, c->series_phase ? 1 : 0, {}, n_steps};

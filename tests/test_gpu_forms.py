@@ -68,3 +68,32 @@ def test_long_rows_take_dense_products(make, precision):
 def test_short_rows_take_the_series(make, precision):
     default, dense, series = states(make(), precision, (-1, 0, 1))
     assert np.array_equal(default, series) and not np.array_equal(default, dense)
+
+
+def vectors(wl, precision, forms):
+    sol = P.Solver(wl, precision)
+    psi = W.haar_psi(sol.n, 3)
+    out = []
+    for form in forms:
+        print(f"pure {wl['name']} N={sol.n} {precision} form={form}", flush=True)
+        sol.set_products(form)
+        sol.set_psi(psi)
+        sol.step_pure(3)
+        out.append(sol.get_psi())
+    sol.close()
+    return out
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("make", [lambda: star(65), lambda: star(501), lambda: star(2048), lambda: ring(257, 32),
+                                  lambda: ring(2048, 32), lambda: ring(4097, 32)])
+def test_pure_long_rows_take_dense(make, precision):
+    default, dense = vectors(make(), precision, (-1, 0))
+    assert np.array_equal(default, dense)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("make", [lambda: ring(64, 2), lambda: ring(2048, 2), lambda: ring(4097, 4)])
+def test_pure_short_rows_take_the_series(make, precision):
+    default, dense, series = vectors(make(), precision, (-1, 0, 1))
+    assert np.array_equal(default, series) and not np.array_equal(default, dense)
