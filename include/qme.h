@@ -565,8 +565,7 @@ qme_status qme_set_fused(qme_ctx *ctx, int32_t enable);
  * step by rounding only.  Steps by the series (qme_set_products) fold in every
  * precision: one pass per step rotates each row, applies the factor and starts
  * the next step's rotation, and the renormalisation factor stays pending until
- * the call's closing pass.  (A profiled call, qme_profile_enable, runs a step's
- * two passes: the same arithmetic.)  enable: 0 or 1, else QME_E_ARG. */
+ * the call's closing pass.  enable: 0 or 1, else QME_E_ARG. */
 qme_status qme_set_fold(qme_ctx *ctx, int32_t enable);
 
 /* Tile body of the FP32 products whose second operand is read by rows (all
@@ -615,7 +614,14 @@ qme_status qme_profile_enable(qme_ctx *ctx, int32_t enable);
  * summed duration in milliseconds and the number of launches since the last
  * enable: kind 0 = first product (full), 1 = second product (lower tiles),
  * 2 = trace/sink pass, 3 = decoherence pass.  Arrays of 4 (either may be
- * NULL).  Recording stays enabled. */
+ * NULL).  Recording stays enabled.
+ * Folded steps by the series: after qme_set_products(ctx, 1) the launches are
+ * those of an unprofiled call -- where a step is one pass, kind 0 is the
+ * call's first pass, kind 1 one pass per step and kind 2 the call's last trace.
+ * In the automatic choice (-1) a profiled call runs each step's two passes
+ * instead, and the trace launches that the dense step would have: the same
+ * arithmetic and bits, the kinds and counts of the dense products, but not the
+ * kernels that an unprofiled call runs. */
 qme_status qme_profile_read(qme_ctx *ctx, double *total_ms, int64_t *launches);
 
 /* Release a context and its device tables. NULL is ignored. */

@@ -364,10 +364,12 @@ static bool trace_in_first_product(const qme_ctx *c, T *area) {
 // first rotation without leaving the compute unit; W^dag alternates between
 // the workspace's plane pairs), the last second pass into the state.  Step k's
 // trace is formed beside the pass after the one that leaves its diagonal, and
-// its factor stays pending: the closing pass applies the last one.  Under
-// profiling every step runs its two passes (the same arithmetic, bitwise), and
-// the trace keeps the launches that the dense step would give it, so that the
-// launch counts per kind mean the same for both forms.
+// its factor stays pending: the closing pass applies the last one.  A profiled
+// call records these launches where the series was asked for
+// (qme_set_products(ctx, 1)).  In the automatic choice it runs every step's two
+// passes instead (the same arithmetic, bitwise), with the trace launches that the
+// dense step would give it, so that its counts per kind are those of the dense
+// products.
 template <typename T>
 static hipError_t series_fold_steps(qme_ctx *c, void *state, int64_t n_steps, void *ws,
                                     hipStream_t s) {
@@ -403,8 +405,14 @@ static hipError_t series_fold_steps(qme_ctx *c, void *state, int64_t n_steps, vo
     da.pend = pend_of(k);
     return launch_trace<T>(da, s);
   };
+  auto diag_trace = [&](int64_t k, hipError_t e) {
+    if (e == hipSuccess) e = trace(k);
+    if (e == hipSuccess) e = mark(c, s, 2);
+    launch_timer() = nullptr;   // the closing pass is no step's kernel
+    return e;
+  };
   hipError_t e = hipSuccess;
-  if (c->profiling) {
+  if (c->profiling && c->products != 1) {
     const bool beside = trace_in_first_product<T>(c, split_area_of<T>(c, ws));
     for (int64_t k = 0; k < n_steps && e == hipSuccess; ++k) {
       e = mark(c, s, -1);
@@ -416,16 +424,23 @@ static hipError_t series_fold_steps(qme_ctx *c, void *state, int64_t n_steps, vo
       if (e == hipSuccess && (!beside || k == n_steps - 1)) e = trace(k);
       if (e == hipSuccess) e = mark(c, s, 2);
     }
-    launch_timer() = nullptr;   // the closing pass is no step's kernel
+    launch_timer() = nullptr;
   } else {
-    e = launch_series_pass<T>(pass(x_re, y, -1, -1), kSeriesFirst, s);
-    for (int64_t k = 0; k + 1 < n_steps && e == hipSuccess; ++k)
+    // a record of kind 1 per step: the pass that holds its second rotation
+    e = mark(c, s, -1);
+    if (e == hipSuccess) e = launch_series_pass<T>(pass(x_re, y, -1, -1), kSeriesFirst, s);
+    if (e == hipSuccess) e = mark(c, s, 0);
+    for (int64_t k = 0; k + 1 < n_steps && e == hipSuccess; ++k) {
       e = launch_series_pass<T>(pass(y + (k & 1) * 2 * pe, y + (1 - (k & 1)) * 2 * pe, k, k - 1),
                                 kSeriesStep, s);
+      if (e == hipSuccess) e = mark(c, s, 1);
+      if (e == hipSuccess) e = mark(c, s, -1);
+    }
     const int64_t k = n_steps - 1;
     if (e == hipSuccess)
       e = launch_series_pass<T>(pass(y + (k & 1) * 2 * pe, x_re, k, k - 1), kSeriesFold, s);
-    if (e == hipSuccess) e = trace(k);
+    if (e == hipSuccess) e = mark(c, s, 1);
+    e = diag_trace(k, e);
   }
   return e == hipSuccess ? launch_series_close<T>(x_re, x_im, c->ld, c->n, aux + 4, s) : e;
 }

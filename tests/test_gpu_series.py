@@ -319,3 +319,34 @@ def test_single_workgroup_kernels_against_oracle(make, precision):
 ])
 def test_single_workgroup_widths_against_oracle(make, precision):
     test_single_workgroup_kernels_against_oracle(make, precision)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64", "bf16x3"])
+@pytest.mark.parametrize("n", [128, 513, 2048])
+def test_profiled_series_runs_the_callers_launches(n, precision):
+    """After qme_set_products(ctx, 1) a profiled call of folded steps records the
+    launches of an unprofiled one: the call's first pass, one pass per step and
+    the last trace; a stride samples the steps; the state's bits are the same, and
+    those of the two passes per step that a profiled call runs by default."""
+    wl = cavity_chain(n)
+    psi = W.haar_psi(n, 3)
+    out = []
+    for form, every in ((1, 0), (1, 1), (1, 3), (-1, 1)):
+        sol = P.Solver(wl, precision)
+        sol.set_products(form)
+        sol.set_rho(np.outer(psi, psi.conj()), sink=0.125)
+        sol.profile(every)
+        print(f"profiled series N={n} {precision} form={form} every={every}", flush=True)
+        for k in (1, 2, 4):
+            sol.step(k)
+        torch.cuda.synchronize()
+        counts = [c for _, c in sol.profile_read().values()]
+        # steps 0, 3 and 6 are sampled; of the calls' first ones 0 and 3, of the last ones 0 and 6
+        if form == 1:
+            assert counts == {0: [0, 0, 0, 0], 1: [3, 7, 3, 0], 3: [2, 3, 2, 0]}[every]
+        else:
+            assert counts[:2] == [7, 7]
+        out.append((*sol.get_rho(), sol.observe()[1]))
+        sol.close()
+    for got in out[1:]:
+        assert np.array_equal(got[0], out[0][0]) and got[1:] == out[0][1:]
