@@ -362,7 +362,8 @@ static bool trace_in_first_product(const qme_ctx *c, T *area) {
 // Folded steps by the series: the first step's first pass, one pass per further
 // step (kSeriesStep: the rows go through a step's second and the next one's
 // first rotation without leaving the compute unit; W^dag alternates between
-// the workspace's plane pairs), the last second pass into the state.  Step k's
+// the workspace's plane pairs), the last second pass into the state; or two
+// passes per step with the state between them (series_one_pass).  Step k's
 // trace is formed beside the pass after the one that leaves its diagonal, and
 // its factor stays pending: the closing pass applies the last one.  A profiled
 // call records these launches where the series was asked for
@@ -412,8 +413,9 @@ static hipError_t series_fold_steps(qme_ctx *c, void *state, int64_t n_steps, vo
     return e;
   };
   hipError_t e = hipSuccess;
-  if (c->profiling && c->products != 1) {
-    const bool beside = trace_in_first_product<T>(c, split_area_of<T>(c, ws));
+  const bool as_dense = c->profiling && c->products != 1;
+  if (as_dense || !series_one_pass(c->n, int(c->elem), c->series_order)) {
+    const bool beside = !as_dense || trace_in_first_product<T>(c, split_area_of<T>(c, ws));
     for (int64_t k = 0; k < n_steps && e == hipSuccess; ++k) {
       e = mark(c, s, -1);
       if (e == hipSuccess)

@@ -435,6 +435,7 @@ template <typename T>
 hipError_t launch_series_close(T *re, T *im, int64_t ld, int64_t n, const double *factor, hipStream_t s);
 int series_slot_bytes(int64_t n);        // LDS bytes per plane of one state of a workgroup's rows
 int series_slices_per_wave(int64_t n);   // slices of 64 states that a wave takes
+bool series_one_pass(int64_t n, int elem, int order);   // folded steps: kSeriesStep, else two passes
 template <typename T>
 hipError_t launch_series_pass(const SeriesArgs<T> &a, int mode, hipStream_t s);
 

@@ -132,6 +132,21 @@ static SeriesShape series_shape(int64_t n) {
 int series_slot_bytes(int64_t n) { return std::min(series_shape(n).bytes, 16); }
 int series_slices_per_wave(int64_t n) { return series_shape(n).slices; }
 
+// A folded step in one pass saves a round trip of the state, but past N = 4096 its
+// body holds more than the registers (101 of them spilled per lane at five slices
+// per wave, 112 and more at eight), so that a long series makes up for the round
+// trip.  Measured (us per step, one pass / two, four couplings per state): FP32 N
+// = 4131 order 3 294 / 284, 5 374 / 344, 7 454 / 405, 10 573 / 495; 5120 order 3 342
+// / 350, 5 421 / 409; 6000 order 5 1109 / 1127, 7 1365 / 1327, 10 1744 / 1648; FP64 N =
+// 4131 order 10 1764 / 1749 and 5120 2211 / 2256; 6000 order 4 3072 / 3069, 5 3647 /
+// 3575, 10 7140 / 6656.  Up to N = 4096 one pass is the faster or equal (2048 FP32
+// 36 / 43, 4096 order 7 251 / 255).
+bool series_one_pass(int64_t n, int elem, int order) {
+  if (n <= 4096) return true;
+  if (elem == 8) return n <= 5120 || order < 5;
+  return order < (n <= 5120 ? 5 : 7);
+}
+
 // A step is as slow as the longest wave of a workgroup, or as the workgroup's
 // LDS reads where all its rows are long, times the rounds of workgroups on the
 // device: not as the mean row of H.  The figures are fits to steps timed on the

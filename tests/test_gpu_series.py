@@ -350,3 +350,31 @@ def test_profiled_series_runs_the_callers_launches(n, precision):
         sol.close()
     for got in out[1:]:
         assert np.array_equal(got[0], out[0][0]) and got[1:] == out[0][1:]
+
+
+@pytest.mark.parametrize("n,precision,theta,one", [
+    (4096, "fp32", 0.2, True), (4097, "fp32", 0.004, True), (4097, "fp32", 0.2, False),
+    (5121, "fp32", 0.04, True), (5121, "fp32", 0.2, False),
+    (4097, "fp64", 0.2, True), (5121, "fp64", 0.2, False)])
+def test_large_folded_steps_one_pass_or_two(n, precision, theta, one):
+    """Past N = 4096 a long series steps in two passes (its one-pass body spills),
+    a short one in one; the bits are those of the other form, which a profiled
+    call runs by default."""
+    wl = cavity_chain(n, dt=theta / 0.4)      # |H dt| = 2 mu dt
+    psi = W.haar_psi(n, 3)
+    out = []
+    for form in (1, -1):
+        sol = P.Solver(wl, precision)
+        sol.set_products(form)
+        sol.set_rho(np.outer(psi, psi.conj()), sink=0.125)
+        sol.profile(True)
+        print(f"one pass or two N={n} {precision} |H dt|={theta} form={form}", flush=True)
+        for k in (1, 2):
+            sol.step(k)
+        torch.cuda.synchronize()
+        counts = [c for _, c in sol.profile_read().values()]
+        if form == 1:
+            assert counts == ([2, 3, 2, 0] if one else [3, 3, 2, 0])
+        out.append((*sol.get_rho(), sol.observe()[1]))
+        sol.close()
+    assert np.array_equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
