@@ -587,8 +587,11 @@ qme_status qme_set_direct_loads(qme_ctx *ctx, int32_t mode);
  * element and term in place of N), -1 (default) by the series where it is the
  * faster form (a rule on N, H's couplings and |H dt|) and qme_set_split has
  * not asked for split products.  Tiles, splits and direct loads are knobs of
- * the dense products.  The forms agree to rounding.  1 for a context without
- * a series form: QME_E_UNSUPPORTED; other values: QME_E_ARG. */
+ * the dense products.  The forms agree to rounding.  Systems of up to 32 states
+ * take the entries of dU or, by default where it is the faster form, the series
+ * inside their single-workgroup path (qme_set_fused): 0 leaves only dU, 1 is
+ * refused.  1 for a context without row passes of the series:
+ * QME_E_UNSUPPORTED; other values: QME_E_ARG. */
 qme_status qme_set_products(qme_ctx *ctx, int32_t form);
 
 /* Graph replay of qme_step (off by default): with enable = 1, a call of

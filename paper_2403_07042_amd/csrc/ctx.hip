@@ -551,7 +551,7 @@ static qme_status step_impl(qme_ctx *c, void *state, int64_t n_steps, void *ws,
                    c->ld, int(c->n), c->model.dt, c->d, c->leak, c->pi, c->cg,
                    c->jt.n_gather, n_steps, c->trw, c->du_row_max, {}};
     static_assert(sizeof(a.series.ratio) == sizeof(c->series_ratio), "one length of series");
-    if (c->small_order > 0) {
+    if (c->small_order > 0 && c->products != 0) {
       a.series.order = c->small_order;
       a.series.entries = c->small_entries;
       a.series.slot_bytes = series_slot_bytes(c->n);

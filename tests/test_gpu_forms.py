@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as W
+from oracle import evolve as ev
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +98,31 @@ def test_pure_long_rows_take_dense(make, precision):
 def test_pure_short_rows_take_the_series(make, precision):
     default, dense, series = vectors(make(), precision, (-1, 0, 1))
     assert np.array_equal(default, series) and not np.array_equal(default, dense)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("make", [
+    lambda: W.photon_lattice(4, 3, mu=0.02, gamma=0.05, dt=0.01, atoms_per_site=0, g=0.0),  # N = 12
+    lambda: W.jc_single(cap=8),                                                             # N = 18
+    lambda: W.photon_lattice(4, 4, mu=0.1, g=0.1, gamma=0.05, dt=0.1)])                     # N = 32
+def test_small_systems_obey_form_zero(make, precision):
+    """Systems that step by the series in their single workgroup by default: form
+    0 multiplies by dU instead, and both agree with the oracle."""
+    wl = make()
+    s = ev.System(wl)
+    psi = W.haar_psi(s.n, 13)
+    rho0 = np.outer(psi, psi.conj())
+    ref, sink = ev.evolve(s, rho0, 60)
+    sol = P.Solver(wl, precision)
+    out = []
+    for form in (-1, 0, -1):
+        print(f"single workgroup N={sol.n} {precision} form={form}", flush=True)
+        sol.set_products(form)
+        sol.set_rho(rho0)
+        sol.step(60)
+        out.append(sol.get_rho())
+    sol.close()
+    assert np.array_equal(out[0][0], out[2][0]) and not np.array_equal(out[0][0], out[1][0])
+    tol = {"fp32": 1e-5, "fp64": 1e-12}[precision]
+    for rho, got in out:
+        assert np.abs(rho - ref).max() < tol * np.abs(ref).max() and abs(got - sink) < tol
