@@ -500,15 +500,15 @@ hipError_t launch_small_steps(const SmallArgs<T> &a, hipStream_t s) {
     SmallArgs<T> b = a;
     b.steps = std::min<int64_t>(kSmallStepsPerLaunch, a.steps - done);
     // up to eight entries in a row of dU: two sweeps over them against two per
-    // term of the series (N = 32, three channels, FP64: 5.1 against 5.6 us per
-    // step); else the series while H's rows have up to eight (N = 32 lattice
-    // 17.0 -> 2.7 us FP32, 16.6 -> 4.8 FP64; N = 12 2.4 -> 1.2 and 2.0).  Of 17
-    // to 22 states the series takes both (N = 18 FP64, two leaks, a call of 1 /
-    // 100 steps: 13.2 / 335 us by the rows of dU, 6.0 / 267 by the series, 9.4 /
-    // 695 in the general kernel)
+    // term of the series (us per step, rows of dU / series: N = 18 with blocks of
+    // two to eight states FP32 0.8 ... 1.0 / 1.4 ... 3.0, FP64 0.9 ... 1.2 / 2.5 ...
+    // 3.4; N = 32, three channels, FP64 5.1 / 5.6); else the series while H's rows
+    // have up to eight (N = 32 lattice 17.0 -> 2.7 us FP32, 16.6 -> 4.8 FP64; N =
+    // 12 2.4 -> 1.2 and 2.0).  A call of one step takes about as long by either (N =
+    // 18 FP32 7.8 / 6.9, FP64 8.2 / 8.1; 9.4 in the general kernel).
     hipError_t e;
     const bool series = a.n_gather <= 6 && a.series.order > 0 && a.series.entries <= 8;
-    if (a.n_gather <= 6 && a.row_max <= 8 && !(series && a.n > 16 && a.n <= 22))
+    if (a.n_gather <= 6 && a.row_max <= 8)
       e = a.n <= 8 ? launch_small_rows<T, 64>(b, s)
           : a.n <= 16 ? launch_small_rows<T, 256>(b, s)
           : a.n <= 22 ? launch_small_rows<T, 512>(b, s) : launch_small_rows<T, 1024>(b, s);

@@ -103,7 +103,7 @@ def test_pure_short_rows_take_the_series(make, precision):
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
 @pytest.mark.parametrize("make", [
     lambda: W.photon_lattice(4, 3, mu=0.02, gamma=0.05, dt=0.01, atoms_per_site=0, g=0.0),  # N = 12
-    lambda: W.jc_single(cap=8),                                                             # N = 18
+    lambda: W.photon_lattice(18, 1, mu=0.02, gamma=0.05, dt=0.01, atoms_per_site=0, g=0.0),
     lambda: W.photon_lattice(4, 4, mu=0.1, g=0.1, gamma=0.05, dt=0.1)])                     # N = 32
 def test_small_systems_obey_form_zero(make, precision):
     """Systems that step by the series in their single workgroup by default: form
@@ -126,3 +126,13 @@ def test_small_systems_obey_form_zero(make, precision):
     tol = {"fp32": 1e-5, "fp64": 1e-12}[precision]
     for rho, got in out:
         assert np.abs(rho - ref).max() < tol * np.abs(ref).max() and abs(got - sink) < tol
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("cap", [7, 8, 10, 11])
+def test_short_rows_of_du_in_one_workgroup(cap, precision):
+    """One cavity and one atom, N = 16, 18, 22, 24: dU's rows have two entries, so
+    its products are the faster form and the default at every N."""
+    wl = W.jc_single(cap=cap)
+    default, dense = states(wl, precision, (-1, 0))
+    assert np.array_equal(default, dense)
