@@ -40,6 +40,7 @@
 #include "ctx.hpp"
 #include "device.hpp"
 #include "lane_sums.hpp"
+#include "lds_barrier.hpp"
 #include "model.hpp"
 #include "qme.h"
 
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(NT, NT / 256) void pure_series_kernel(PureSeriesArg
     }
     cplx t[S];
     for (int k = p.order; k >= 1; --k) {
-      __syncthreads();
+      lds_barrier();
       const unsigned char *v = lds + (TWO ? flip * buffer : 0);
       if constexpr (K == 2) {
         // (the packed slots are unpacked here, in each term: as invariants of
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(NT, NT / 256) void pure_series_kernel(PureSeriesArg
       }
       flip ^= 1;
       if (k == 1) break;
-      if constexpr (!TWO) __syncthreads();
+      if constexpr (!TWO) lds_barrier();
       const T w = T(p.ratio[k]);   // v <- x - i w K v
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(NT, NT / 256) void pure_series_kernel(PureSeriesArg
     }
     // (one buffer: every wave has read v before the next step writes it; one
     // term: the norms have had no barrier yet)
-    if (!TWO || p.order == 1) __syncthreads();
+    if (!TWO || p.order == 1) lds_barrier();
     static_assert(W == 4 || W == 16, "a row of lanes, or four, sums the norms");
     double sum = row_sum(norms[lane & (4 * W - 1)]);
     if constexpr (W == 16) {

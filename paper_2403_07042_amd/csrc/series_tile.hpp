@@ -36,6 +36,7 @@
 
 #include "device.hpp"
 #include "dissipate_tile.hpp"
+#include "lds_barrier.hpp"
 
 namespace qme {
 
@@ -52,18 +53,6 @@ __device__ __forceinline__ double series_uniform(double x) {
   const long long b = __builtin_bit_cast(long long, x);
   const int lo = __builtin_amdgcn_readfirstlane(int(b)), hi = __builtin_amdgcn_readfirstlane(int(b >> 32));
   return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | unsigned(lo));
-}
-
-// __syncthreads with its wait for the wave's own LDS accesses spelt out.  The
-// compiler left that wait out at the head of the loop over the terms, whose
-// writes of v come at its end (ds_write, branch, s_barrier), so another wave
-// could read v before it was written: a few elements of a batch of 256 systems
-// differed in the last place between runs.
-__device__ __forceinline__ void series_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0); vmcnt and expcnt not waited for
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 template <typename T>
@@ -216,7 +205,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   }
 
   for (int k = a.order; k >= 1; --k) {
-    series_barrier();
+    lds_barrier();
 #pragma unroll
     for (int s = 0; s < S; ++s) {
 #pragma unroll
@@ -260,7 +249,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
       }
     }
     if (k == 1) break;
-    series_barrier();
+    lds_barrier();
     const T w = sgn * T(a.ratio[k]);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -332,13 +321,13 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
   if constexpr (MODE == kSeriesFold || MODE == kSeriesStep) decohere();
   if constexpr (MODE == kSeriesStep) {
     fetch_first();
-    series_barrier();   // every wave has read v
+    lds_barrier();   // every wave has read v
     rotate();
     finish();
   }
   // (the row passes hand their results to LDS, by state, so that the rows are
   // written in order: the slots' order would leave parts of lines)
-  if constexpr (kRows) series_barrier();
+  if constexpr (kRows) lds_barrier();
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const int slot = (wave * S + s) * 64 + lane;
@@ -358,7 +347,7 @@ __device__ __forceinline__ void series_rows(const SeriesArgs<T> &a, int group, u
     if constexpr (kRows) put(lds, int(c), w_re, w_im);
   }
   if constexpr (kRows) {
-    series_barrier();
+    lds_barrier();
     unit w_re[S], w_im[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {

@@ -23,6 +23,7 @@
 // 32 (FP32, three channels) 20.4 -> 1.6.
 #include "device.hpp"
 #include "lane_sums.hpp"
+#include "lds_barrier.hpp"
 
 #include <algorithm>
 
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(NT) void small_rows_kernel(SmallArgs<T> p) {
   const bool in = i < n, low = in && j <= i;
   const int e = in ? i * kSmallLd + j : 0, ei = in ? i : 0, ej = in ? j : 0;
   if (in) s_rho[e] = small_pair<T>(p.re[i * p.ld + j], p.im[i * p.ld + j]);
-  __syncthreads();
+  lds_barrier();
   // this element's row i of dU against row j of rho, row i of T against row j
   // of dU
   int at1[L], at2[L];
@@ -316,7 +317,7 @@ __global__ __launch_bounds__(NT) void small_rows_kernel(SmallArgs<T> p) {
     }
     const cplx t = small_pair<T>(cr + own[0], ci + own[1]);
     if (in) s_t[e] = t;
-    __syncthreads();
+    lds_barrier();
     // Z = T + T conj(dU), lower triangle
     cr = ci = T(0);
 #pragma unroll
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(NT) void small_rows_kernel(SmallArgs<T> p) {
     }
     const cplx z = small_pair<T>(cr + t[0], ci + t[1]);
     if (low) s_z[e] = z;
-    __syncthreads();
+    lds_barrier();
     // trace, lost probability and renormalisation, in every wave
     const double zd = double(s_z[el.dw][0]);
     double xr, xi;
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(NT) void small_rows_kernel(SmallArgs<T> p) {
       s_rho[e] = small_pair<T>(a, b);
       s_rho[j * kSmallLd + i] = small_pair<T>(a, i == j ? b : -b);
     }
-    __syncthreads();
+    lds_barrier();
     own = s_rho[e];
   }
   if (in) {
@@ -391,12 +392,12 @@ __global__ __launch_bounds__(NT) void small_series_kernel(SmallArgs<T> p) {
   SmallElement<T, G> el;
   el.load(p, ei, ej, lane);
   SmallScalars sc{p.aux[0], p.aux[1], p.aux[2], p.aux[3], p.aux[4]};
-  __syncthreads();
+  lds_barrier();
   if (d0 < D && slot < n) {
     s_at[d0][s_state[slot]] = has ? s_state[to] : 0;
     s_k[d0][s_state[slot]] = k;
   }
-  __syncthreads();
+  lds_barrier();
   // K's rows j and i as neighbours along this element's row and column
   int at1[D], at2[D];
   T k1[D], k2[D];
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(NT) void small_series_kernel(SmallArgs<T> p) {
     cplx t;
     if (in) s_v[flip][e] = own;
     for (int m = q.order; m >= 1; --m) {
-      __syncthreads();
+      lds_barrier();
       const cplx *v = s_v[flip];
       t = small_pair<T>(0, 0);
 #pragma unroll
@@ -444,7 +445,7 @@ __global__ __launch_bounds__(NT) void small_series_kernel(SmallArgs<T> p) {
     // (the array that no wave reads any more)
     cplx *s_z = s_v[flip];
     if (low) s_z[e] = z;
-    __syncthreads();
+    lds_barrier();
     const double zd = double(s_z[el.dw][0]);
     double xr, xi;
     el.decohere(z, s_z, xr, xi);
@@ -457,7 +458,7 @@ __global__ __launch_bounds__(NT) void small_series_kernel(SmallArgs<T> p) {
       s_x[e] = small_pair<T>(a, b);
       s_x[j * kSmallLd + i] = small_pair<T>(a, i == j ? b : -b);
     }
-    __syncthreads();
+    lds_barrier();
     x = s_x[e];
     flip ^= 1;
   }
