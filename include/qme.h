@@ -594,6 +594,10 @@ qme_status qme_set_direct_loads(qme_ctx *ctx, int32_t mode);
  * QME_E_UNSUPPORTED; other values: QME_E_ARG. */
 qme_status qme_set_products(qme_ctx *ctx, int32_t form);
 
+/* The form that qme_step takes now: 1 the row passes of the series, 0 any
+ * other (dense products, or the single-workgroup path). */
+qme_status qme_get_products(const qme_ctx *ctx, int32_t *form);
+
 /* Graph replay of qme_step (off by default): with enable = 1, a call of
  * n_steps on a given (state, workspace) pair is captured once into a
  * hipGraph on a private stream and replayed onto the caller's stream with

@@ -354,6 +354,14 @@ class Solver:
         it is faster."""
         L.check(self.lib.qme_set_products(self.ctx, int(form)))
 
+    @property
+    def products(self) -> int:
+        """The form the steps take now: 1 the series, 0 dense products (or
+        the single-workgroup path)."""
+        form = c_int32()
+        L.check(self.lib.qme_get_products(self.ctx, byref(form)))
+        return form.value
+
     def set_graph(self, enable: bool):
         """Replay qme_step runs from captured hipGraphs (off by default)."""
         L.check(self.lib.qme_set_graph(self.ctx, int(bool(enable))))

@@ -9,6 +9,10 @@ candidate is timed on the real step (median of several trials of a few steps,
 on a scratch copy of the state so the caller's state does not advance) and
 the fastest is applied.  Results are cached per (GPU architecture,
 precision, N, ld) in $QME_TUNE_CACHE (default ~/.cache/qme_mi355x/tune.json).
+These are knobs of the dense products: a solver that steps by the series
+(Solver.products) keeps what it has, and a cached entry says which form it
+is of ("form"), so that one of the other form, or of a version before the
+entries said so, is never applied.
 
 With the split off, tile choice among tiles of one matrix-core shape never
 changes results: FP32 64- and 128-tiles (32x32 MFMA) and FP64 32- and
@@ -86,11 +90,22 @@ def _time(torch, fn, trials: int) -> float:
 def tune_solver(sol, steps: int = 4, trials: int = 3, use_cache: bool = True,
                 path: str | None = None):
     """Pick and apply the fastest (tile1, tile2, split) for this solver;
-    returns it."""
+    returns it.  A solver that steps by the series is left as it is: its
+    present tiles and no split are returned, nothing is timed."""
     torch = sol.torch
     key = solver_key(_arch(torch), sol.precision, sol.n, sol.ld)
     cache = load_cache(path) if use_cache else {}
-    if key in cache and "split" in cache[key]:
+    if sol.products == 0:
+        # (an explicit set_split(True) keeps a sparse model on dense products;
+        # without it the context takes the faster form)
+        sol.set_split(False)
+    if sol.products == 1:
+        best = tuple(sol.tiles) + (False,)
+        if use_cache and cache.get(key, {}).get("form") != 0:
+            cache[key] = {"tiles": list(best[:2]), "split": False, "form": 1}
+            save_cache(cache, path)
+        return best
+    if cache.get(key, {}).get("form") == 0:
         best = tuple(cache[key]["tiles"]) + (bool(cache[key]["split"]),)
         sol.set_tiles(*best[:2])
         sol.set_split(best[2])
@@ -109,7 +124,7 @@ def tune_solver(sol, steps: int = 4, trials: int = 3, use_cache: bool = True,
     del scratch
     if use_cache:
         cache = load_cache(path)
-        cache[key] = {"tiles": list(best[:2]), "split": best[2],
+        cache[key] = {"tiles": list(best[:2]), "split": best[2], "form": 0,
                       "seconds_per_step": {f"{a}x{b}{'/split' if sp else ''}": t / steps
                                            for (a, b, sp), t in results.items()}}
         save_cache(cache, path)
@@ -134,7 +149,8 @@ def tune_batch(batch, steps: int = 2, trials: int = 3, tiles: bool = True,
     share them), then graph replay on/off and the instance order.  Sizes
     are tuned one at a time, largest first, each over the four tile pairs
     with the other sizes held (coordinate descent on the whole batched
-    step).  Runs advance the batch's states by the steps timed (callers tune
+    step); a size whose instances all step by the series keeps its tiles, one
+    time stands for its four pairs.  Runs advance the batch's states by the steps timed (callers tune
     before setting their initial states, or re-set them afterwards).
     Returns (best, results): best = (use_graph, largest_first, {N: tiles})."""
     torch = batch.torch
@@ -164,6 +180,11 @@ def tune_batch(batch, steps: int = 2, trials: int = 3, tiles: bool = True,
 
     if tiles:
         for n in sizes:
+            if all(s.products == 1 for s in batch.solvers if s.n == n):
+                apply(per_n)
+                sec = timed(True, True)
+                results.update({("tiles", n, t): sec for t in BATCH_TILES})
+                continue
             best_t, best_time = None, None
             for t in BATCH_TILES:
                 trial = dict(per_n)

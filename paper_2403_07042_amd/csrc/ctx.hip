@@ -1514,6 +1514,13 @@ extern "C" qme_status qme_set_products(qme_ctx *c, int32_t form) {
   return QME_OK;
 }
 
+extern "C" qme_status qme_get_products(const qme_ctx *c, int32_t *form) {
+  set_error("");
+  if (!c || !form) { set_error("NULL argument"); return QME_E_ARG; }
+  *form = uses_series(c) ? 1 : 0;
+  return QME_OK;
+}
+
 extern "C" qme_status qme_set_tiles(qme_ctx *c, int32_t tile1, int32_t tile2) {
   set_error("");
   if (!c) { set_error("ctx is NULL"); return QME_E_ARG; }
