@@ -450,10 +450,12 @@ typedef struct qme_batch qme_batch;
  * instance, largest instances first; a run of n steps is captured once into
  * a hipGraph and replayed.  Each instance's two products run in the tile
  * edges of its context (qme_set_tiles; 32 or 64, else QME_E_UNSUPPORTED),
- * read when the batch is created or configured.  Each instance advances
- * exactly as under qme_step with the same tiles, unfolded and unsplit (the
- * same tile arithmetic: bitwise-identical results).  The contexts and
- * states must outlive the batch. */
+ * and each steps in the form of its context (qme_set_products), both read when
+ * the batch is created or configured (qme_batch_config): a knob of a context
+ * that is set later takes effect with the next qme_batch_config only.  Each
+ * instance advances exactly as under qme_step with the same tiles and form,
+ * unfolded and unsplit (the same arithmetic: bitwise-identical results).  The
+ * contexts and states must outlive the batch. */
 qme_status qme_batch_create(qme_ctx *const *ctxs, void *const *states_dev, int32_t count,
                             qme_batch **out);
 
@@ -464,8 +466,8 @@ qme_status qme_batch_workspace_size(const qme_batch *batch, size_t *bytes);
 /* Whether runs are captured into (and replayed from) a hipGraph per
  * (n_steps, workspace), and whether larger instances come first in each
  * phase launch.  Rebuilds the batch's tables from the contexts' current
- * tiles (set them with qme_set_tiles, then call this) and drops earlier
- * captures.  Synchronises the device. */
+ * tiles and forms (set them with qme_set_tiles and qme_set_products, then call
+ * this) and drops earlier captures.  Synchronises the device. */
 qme_status qme_batch_config(qme_batch *batch, int32_t use_graph, int32_t largest_first);
 
 /* Persistent form of the batched run (off by default): with enable = 1 a run
@@ -537,8 +539,12 @@ qme_status qme_get_tiles(const qme_ctx *ctx, int32_t *tile1, int32_t *tile2);
  * tiles, their partials in the workspace's slots (qme_workspace_size).  A
  * reduce pass sums each tile's chunks in k order.  Results differ from the
  * unsplit products only by FP rounding (the k sum is regrouped) and are
- * deterministic for a given (ld, tile, device).  enable: 0 or 1, else
- * QME_E_ARG. */
+ * deterministic for a given (ld, tile, device).  A call with 1 asks for split
+ * products: a context in the automatic choice of the form (qme_set_products
+ * -1) then takes dense products even where the series is the faster form
+ * (many times faster for a sparse H), until a call with 0 or
+ * qme_set_products(ctx, 1).  Leave the setting alone for the fastest step;
+ * qme_get_products tells the form.  enable: 0 or 1, else QME_E_ARG. */
 qme_status qme_set_split(qme_ctx *ctx, int32_t enable);
 
 /* Single-workgroup path (on by default): for FP32 and FP64 contexts with

@@ -334,7 +334,9 @@ class Solver:
     def set_split(self, enable: bool):
         """k-splits of the products on (default) or off: the tail of the
         lower-triangle product, and every tile of a launch too small for the
-        device (FP32 / FP64)."""
+        device.  True asks for them: a solver whose default is the series
+        then steps by dense products, which is slower there, until False or
+        set_products(1)."""
         L.check(self.lib.qme_set_split(self.ctx, int(bool(enable))))
 
     def set_fold(self, enable: bool):
@@ -388,7 +390,9 @@ class Solver:
 
 class Batch:
     """Many FP32 solvers stepped together: one launch per phase covers every
-    instance's tiles; a run of steps is replayed from one captured hipGraph."""
+    instance's tiles; a run of steps is replayed from one captured hipGraph.
+    The solvers' tiles and forms (set_tiles, set_products, set_split) are read
+    here and by config(): set later, they take effect with the next config()."""
 
     def __init__(self, solvers):
         self.solvers = list(solvers)

@@ -136,3 +136,35 @@ def test_short_rows_of_du_in_one_workgroup(cap, precision):
     wl = W.jc_single(cap=cap)
     default, dense = states(wl, precision, (-1, 0))
     assert np.array_equal(default, dense)
+
+
+def test_batch_takes_the_forms_at_config():
+    """An instance's form is read when the batch is made and by config()."""
+    wl = ring(200, 4)
+    sol = P.Solver(wl, "fp32")
+    psi = W.haar_psi(sol.n, 3)
+    rho0 = np.outer(psi, psi.conj())
+    solo = P.Solver(wl, "fp32")
+    solo.set_fold(False)
+    ref = {}
+    for form in (-1, 0):
+        solo.set_products(form)
+        if form == 0:
+            solo.set_split(False)
+        solo.set_rho(rho0)
+        solo.step(2)
+        ref[form] = solo.get_rho()[0]
+    solo.close()
+    assert not np.array_equal(ref[-1], ref[0])
+    b = P.Batch([sol])
+    for form, config, expected in ((-1, False, -1), (0, False, -1), (0, True, 0), (-1, True, -1)):
+        sol.set_products(form)
+        if config:
+            b.config()
+        sol.set_rho(rho0)
+        b.step(2)
+        torch.cuda.synchronize()
+        assert np.array_equal(sol.get_rho()[0], ref[expected]), (form, config)
+    assert sol.products == 1
+    b.close()
+    sol.close()
