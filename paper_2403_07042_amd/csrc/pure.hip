@@ -20,13 +20,16 @@
 //
 // pure_series_kernel: where the context has the propagator's series
 // (series_tile.hpp), all steps of a call in one launch, one workgroup per
-// vector.  The vector, the terms and H's rows stay on the compute unit: x, the
-// sums and the first entries of each row in registers, the series' v in LDS
-// (real and imaginary part of a state side by side), so a step is `order`
-// gather sweeps with one barrier each (v alternates between two buffers where
-// both fit), and no memory traffic.  What bounds it is the latency of that
-// chain.  N = 4131 plane FP32 (seven terms): 23.3 us per step with dU streamed
-// from HBM (136 MB per step at 5.9 TB/s).
+// vector.  The vector and the terms stay on the compute unit: x, the sums and the
+// first C entries of each row in registers, the series' v in LDS (real and
+// imaginary part of a state side by side), so a step is `order` gather sweeps with
+// one barrier each (v alternates between two buffers where both fit).  Rows of more
+// than C entries (2 to 12, pure_shape) read the rest from memory in every term, and
+// past N = 4096 the registers do not hold a lane's share (scratch per lane 84 bytes
+// FP32 and 116 FP64 up to N = 5120, 290 and 370 past it; 12 to 28 from 3073 to
+// 4096); elsewhere a step has no memory traffic, and the latency of that chain
+// bounds it.  N = 4131 plane FP32 (seven terms): 23.3 us per step with dU streamed
+// from HBM (136 MB per step at 5.9 TB/s), 6.4 so.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

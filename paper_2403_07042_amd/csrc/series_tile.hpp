@@ -14,12 +14,14 @@
 // all its rows with one LDS read per plane.  The series runs in Horner form
 //   v <- x + (A v) / k,  k = order .. 2,   delta = A v,   result = x + delta,
 // A = +-i K dt with K = H less a shift that is constant on each connected
-// component of H (it commutes with H; e^{-+i shift dt} is applied exactly, in
-// FP64, at the end).  v lives in LDS, x and the sums in registers: a term is
-// one gather sweep and two barriers.  (The coefficients are those of the
-// series economised on |K dt| <= theta, which needs a term or two less:
-// ratio[k] stands for 1 / k.)  x is added in FP64 and the result
-// rounded once.
+// component of H (it commutes with H; where the shifts differ, e^{-+i shift dt} - 1
+// is formed in FP64 by the plan and applied at the end in the storage type, as a
+// small term).  v lives in LDS, x and the sums in registers: a term is one gather
+// sweep and two barriers.  (The coefficients are those of the series economised
+// on |K dt| <= theta, which needs a term or two less: ratio[k] stands for 1 / k.)
+// The result is x + (small terms): the terms are summed in the storage type and the
+// last addition rounds once -- in the storage type, or in FP64 with the decoherence
+// factor where a step is folded.
 //
 // What bounds it: at N = 2048 a pass moves 33.5 MB in and 33.5 MB out (a copy of
 // that size takes 8.4 us) and reads 0.4 GB of LDS per rotation; its loads, terms
@@ -27,9 +29,15 @@
 // of them.  Measured there: 21 + 20 us FP32 (three terms) and 48 + 48 us FP64
 // (four), against 387 + 224 and 844 + 452 us of the dense products; a folded
 // step in one pass (kSeriesStep) 32.8 us FP32 and 83.7 us FP64.  The rest of
-// the range, two passes / one: N = 100 9.0 / 5.8 us FP32 and 13.3 / 7.4 FP64,
-// 500 15.1 / 8.4 and 19.5 / 12.8, 1024 21.4 / 13.6 and 36.7 / 26.7, 4096 161 /
-// 152 and 611 / 540, 8190 1268 / 1171 and 4670 / 4566.
+// the range with series as short, two passes / one: N = 100 9.0 / 5.8 us FP32 and
+// 13.3 / 7.4 FP64, 500 15.1 / 8.4 and 19.5 / 12.8, 1024 21.4 / 13.6 and 36.7 / 26.7,
+// 4096 161 / 152 and 611 / 540.  Longer series and rows, and N past 4096:
+// series_step_us and series_one_pass (series.hip).
+// The registers (128 at four waves per SIMD) do not hold every shape: bytes of
+// scratch per lane in the two passes / in kSeriesStep are none / 96 (FP32) and 112
+// (FP64) at N = 1025 ... 2048, 0 to 20 / 124 and 20 to 48 / 152 up to 4096, 120 to
+// 148 / 280 and 132 to 156 / 304 up to 5120, 164 to 240 / about 305 past it.  There
+// the spilled part of the rows makes the way through memory as well.
 #pragma once
 
 #include <cstdint>
@@ -83,7 +91,8 @@ __device__ __forceinline__ int64_t series_unit(int c, int g, int groups) {
 // symmetry (Herm commutes with every step).
 // MODE kSeriesStep: kSeriesFold and the next step's kSeriesFirst in one: a row
 // of the state is all that its own next pass needs, so it stays in the
-// registers and only the blocks pass through memory, once per step.
+// registers (but for what the shape spills) and only the blocks pass through
+// memory, once per step.
 //
 // The renormalisation factor is a scalar: it stays pending (DissArgs::pend)
 // until the call's closing pass.  Factors near one are applied as x + (small
