@@ -15,8 +15,8 @@ resident in HBM before the timed region starts.
 Prints one JSON line (rank 0, N = 1): value = FP32 time steps per second from
 a run with no profiling, plus the FP64 and split-BF16x3 rates, per-kernel
 durations from a second, profiled run of the same steps (every 8th step's
-kernels launched with start / stop events stamped by their own dispatch; a
-profiled step runs its two passes), the roofline entry of the step's pass, the
+kernels launched with start / stop events stamped by their own dispatch: the
+launches of the unprofiled run), the roofline entry of the step's pass, the
 same steps with dense MFMA products (Solver.set_products(0)) with the matrix
 pipe's fraction in them, and the CPU oracle timed on the host cores.
 """
@@ -39,23 +39,29 @@ PEAK_FP64_MFMA = 78.6       # TFLOP/s, MI355X dense FP64 matrix
 PEAK_BF16_MFMA = 2500.0     # TFLOP/s, MI355X dense bf16 matrix
 PEAK_HBM = 8000.0           # GB/s
 
-# HBM bytes per launch of the first FP32 product, from the FETCH_SIZE /
-# WRITE_SIZE counters (scaled by a plain-copy calibration) recorded in
-# profiles/cgemm_f32_lattice_n2048_hbm_counters.md for this source hash of
-# the kernel's sources; reported as null once they differ.
-TRAFFIC_FP32_PRODUCT = {"bytes": 275295.0 * 1024,
-                        "sha256": "40983a9412742329d3f48aa538ab647a095912872d7d900097592fb380a469f8",
-                        "source": "profiles/cgemm_f32_lattice_n2048_hbm_counters.md"}
-KERNEL_SOURCES = ("cgemm.hip", "cgemm_tile.hpp", "dissipate_tile.hpp")
+# HBM bytes per launch of the one-pass FP32 step and of the first dense FP32
+# product at N = 2048, from the FETCH_SIZE / WRITE_SIZE counters (scaled by a
+# plain-copy calibration) recorded in
+# profiles/cgemm_f32_lattice_n2048_hbm_counters.md for these source hashes of the
+# kernels' sources; reported as null once they differ.
+TRAFFIC_SOURCE = "profiles/cgemm_f32_lattice_n2048_hbm_counters.md"
+TRAFFIC_UNIT = ("HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated; "
+                + TRAFFIC_SOURCE + ")")
+TRAFFIC_FP32_STEP = {"bytes": 109595.0 * 1024,
+                     "sha256": "6bb9b2db3d265506f7782730f9646ea34cfa6bc0e933489691fb94af8174b9da",
+                     "sources": ("series.hip", "series_tile.hpp", "dissipate_tile.hpp")}
+TRAFFIC_FP32_PRODUCT = {"bytes": 275411.0 * 1024,
+                        "sha256": "d49e7fb8633b69d9185f7f28add14f5f592ee8c5e12571cf12902b14083d40bf",
+                        "sources": ("cgemm.hip", "cgemm_tile.hpp", "dissipate_tile.hpp")}
 
 
-def measured_traffic():
+def measured_traffic(kernel):
     import hashlib
     h = hashlib.sha256()
-    for name in KERNEL_SOURCES:
+    for name in kernel["sources"]:
         with open(os.path.join(ROOT, "paper_2403_07042_amd", "csrc", name), "rb") as f:
             h.update(f.read())
-    return TRAFFIC_FP32_PRODUCT["bytes"] if h.hexdigest() == TRAFFIC_FP32_PRODUCT["sha256"] else None
+    return kernel["bytes"] if h.hexdigest() == kernel["sha256"] else None
 
 
 def parse():
@@ -124,7 +130,10 @@ def timed_leg(P, W, torch, wl, precision, steps, warmup, tiles="", tune=False):
     t1 = time.perf_counter()
     pops, trace, sink = sol.observe()
     # profiled pass: each sampled step's kernels carry start / stop events
-    # stamped by their own dispatch, so a duration is the kernel alone
+    # stamped by their own dispatch, so a duration is the kernel alone.  (Asked
+    # for by name, the series' launches are those of the pass above.)
+    if sol.products == 1:
+        sol.set_products(1)
     sol.set_rho(rho0)
     sol.profile(PROFILE_EVERY)
     torch.cuda.synchronize()
@@ -166,9 +175,10 @@ def timed_leg(P, W, torch, wl, precision, steps, warmup, tiles="", tune=False):
 
 
 def kernel_times(prof):
-    """us per sampled step (one first product or pass each): a kind launched on
-    fewer steps (the folded steps' trace, once per call) counts at its share."""
-    sampled = max(prof["product_full"][1], 1)
+    """us per sampled step (one second product or pass each): a kind launched on
+    fewer steps (once per call: the folded steps' trace, and the first pass where a
+    step is one pass) counts at its share."""
+    sampled = max(prof["product_lower"][1], 1)
     return {k: 1e3 * ms / sampled for k, (ms, cnt) in prof.items()}
 
 
@@ -454,7 +464,9 @@ def hydrogen_bond_leg(P, torch, steps=100, warmup=5):
     sol.step(warmup)
     sol.set_rho(rho0)
     dt = _timed(torch, lambda: sol.step(steps))
-    sol.set_rho(rho0)                     # profiled pass of the same steps
+    if sol.products == 1:                 # profiled pass of the same steps
+        sol.set_products(1)
+    sol.set_rho(rho0)
     sol.profile(PROFILE_EVERY)
     _timed(torch, lambda: sol.step(steps))
     prof = sol.profile_read()
@@ -601,7 +613,8 @@ def main():
                           "decoherence factor, one launch per step)",
                 "achieved": tb_s, "peak": PEAK_HBM / 1e3, "unit": "TB/s",
                 "frac": tb_s / (PEAK_HBM / 1e3),
-                "traffic": None,
+                "traffic": measured_traffic(TRAFFIC_FP32_STEP) if prec == "fp32" else None,
+                "traffic_unit": TRAFFIC_UNIT,
                 "per_launch_bytes": state_bytes(main_leg),
                 "per_launch_basis": "both N x N planes of the state read and written once",
                 "avg_launch_us": 1e3 * main_leg["ms_per_step"],
@@ -619,15 +632,14 @@ def main():
         "kernel": f"cgemm_{prec}_kernel<{main_leg['tile1']}, conj_b> "
                   "(first product T = rho + dU rho, full tiles)",
         "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-        "traffic": measured_traffic() if prec == "fp32" else None,
+        "traffic": measured_traffic(TRAFFIC_FP32_PRODUCT) if prec == "fp32" else None,
         "per_launch_flop": executed_per_launch,
         "per_launch_basis": "three real ld x ld x ld products (3M form of the complex "
                             f"product), 6*ld^3 flop, ld = {ld}",
         "avg_launch_us": avg_us,
         "duration_source": "HIP start / stop events stamped by the kernel's own dispatch, "
                            "every 8th step of a profiled pass",
-        "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, "
-                        "copy-calibrated; " + TRAFFIC_FP32_PRODUCT["source"] + ")"}
+        "traffic_unit": TRAFFIC_UNIT}
 
     cpu, parity = None, None
     if args.cpu_steps > 0:
