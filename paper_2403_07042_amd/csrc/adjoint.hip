@@ -370,12 +370,27 @@ __global__ void set_diag_kernel(T *x_re, T *x_im, int64_t ld, int64_t n, const d
 // W = L(B, G) for B = -i tau H by the series of the adjoint of the Frechet
 // derivative of exp: M_1 = G, R_1 = G B, M_{k+1} = (B M_k + R_k) / (k+1),
 // R_{k+1} = R_k B / (k+1), W = sum_k M_k.  H is sparse (CSR, symmetric), so
-// every product is a sparse-times-dense pass, one workgroup per 32 x 32 tile:
-// of all tiles, or of the listed ones (frechet_tiles: elsewhere G is zero and
-// nothing reaches W's entries), where the planes hold zeros in the others.
-// Over all tiles at N = 2048 a term moves 470 MB (62 + 73 us as a right and a
-// left pass); listed (a fifth of the tiles), and both in one, it takes 33 us,
-// bound by the latency of its chains of loads: 1.14 -> 0.35 ms per call.
+// every product is a sparse-times-dense pass: over whole rows, 256 elements a
+// workgroup, the left and the right product of a term in a launch each; or one
+// workgroup per 32 x 32 tile, both in one launch.  Of all tiles, or of the listed
+// ones (frechet_tiles: elsewhere G is zero and nothing reaches W's entries; the
+// planes hold zeros in the others).
+// Tiles reuse what their rows gather and need one launch a term, but a small matrix
+// has too few of them, and a long row of H holds up its tile's 1024 threads.
+// Measured, us per term, rows / tiles: N = 2048 lattice 135 / 33 (a fifth of the
+// tiles listed; bound by the latency of the chains of loads), rows of eight at N =
+// 513 FP64 (every tile listed) 22.8 / 33.4; whole adjoint of eight steps, ms:
+// Jaynes-Cummings N = 18 0.58 / 0.56, TCH N = 144 0.97 / 1.02, lattice N = 288 0.72 /
+// 0.73, 512 0.84 / 0.80, 968 1.33 / 1.19; rows of 32 at N = 1025 9.3 / 8.0, of 64
+// 14.2 / 10.3, a star of N = 501 5.0 / 5.9 and of 2048 97 / 128.
+// listed: the tiles listed (0: no list).
+static bool frechet_by_tiles(const Csr &h, int64_t listed) {
+  int64_t longest = 0;
+  for (int64_t i = 0; i < h.n; ++i) longest = std::max(longest, h.ptr[size_t(i) + 1] - h.ptr[size_t(i)]);
+  const int64_t edge = (h.n + 31) / 32;
+  const bool few = listed > 0 && 4 * listed <= 3 * edge * edge;
+  return longest <= 256 && (h.n <= 32 || h.n >= 1024 || (few && h.n >= 400));
+}
 
 template <typename T>
 __global__ void widen_kernel(const T *gr, const T *gi, double *dr, double *di, int64_t total) {
@@ -386,14 +401,21 @@ __global__ void widen_kernel(const T *gr, const T *gi, double *dr, double *di, i
   }
 }
 
-// The element of a thread in its workgroup's 32 x 32 tile: listed (row and
-// column tile in 16 bits each), or of the whole grid.
-__device__ __forceinline__ void frechet_tile(const int32_t *listed, int64_t &i, int64_t &j) {
-  const int bi = listed ? listed[blockIdx.x] >> 16 : int(blockIdx.y);
-  const int bj = listed ? listed[blockIdx.x] & 65535 : int(blockIdx.x);
-  i = int64_t(bi) * 32 + (threadIdx.x >> 5);
-  j = int64_t(bj) * 32 + (threadIdx.x & 31);
+// The element of a thread: in its workgroup's 32 x 32 tile (TILES; listed, row and
+// column tile in 16 bits each, or of the whole grid), or in a row.
+template <bool TILES>
+__device__ __forceinline__ void frechet_element(const int32_t *listed, int64_t &i, int64_t &j) {
+  if constexpr (TILES) {
+    const int bi = listed ? listed[blockIdx.x] >> 16 : int(blockIdx.y);
+    const int bj = listed ? listed[blockIdx.x] & 65535 : int(blockIdx.x);
+    i = int64_t(bi) * 32 + (threadIdx.x >> 5);
+    j = int64_t(bj) * 32 + (threadIdx.x & 31);
+  } else {
+    i = blockIdx.y;
+    j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  }
 }
+enum { kFrechetLeft = 1, kFrechetRight = 2 };
 
 // (X H)[i][j], the sum over row j of H
 __device__ __forceinline__ void frechet_right(const int64_t *ptr, const int32_t *col,
@@ -409,12 +431,13 @@ __device__ __forceinline__ void frechet_right(const int64_t *ptr, const int32_t 
 }
 
 // W = M (G widened), R = M B
-__global__ __launch_bounds__(1024) void frechet_begin_kernel(
+template <bool TILES>
+__global__ __launch_bounds__(TILES ? 1024 : 256) void frechet_begin_kernel(
     const int64_t *ptr, const int32_t *col, const double *val, const int32_t *listed, double tau,
     const double *mr, const double *mi, double *rr, double *ri, double *wr, double *wi, int64_t n,
     int64_t ld) {
   int64_t i, j;
-  frechet_tile(listed, i, j);
+  frechet_element<TILES>(listed, i, j);
   if (i >= n || j >= n) return;
   double ar, ai;
   frechet_right(ptr, col, val, mr, mi, i, j, ld, ar, ai);
@@ -425,32 +448,38 @@ __global__ __launch_bounds__(1024) void frechet_begin_kernel(
   wi[o] = mi[o];
 }
 
-// M' = inv (B M + R), W += M', R' = inv R B    (row i of B M uses row i of H;
-// B M = -i tau (H M): real part tau Im(HM), imaginary part -tau Re(HM))
-__global__ __launch_bounds__(1024) void frechet_term_kernel(
+// Left: M' = inv (B M + R), W += M'; right: R' = inv R B; PARTS: which of them
+// (row i of B M uses row i of H; B M = -i tau (H M): real part tau Im(HM),
+// imaginary part -tau Re(HM))
+template <bool TILES, int PARTS>
+__global__ __launch_bounds__(TILES ? 1024 : 256) void frechet_term_kernel(
     const int64_t *ptr, const int32_t *col, const double *val, const int32_t *listed, double tau,
     const double *mr, const double *mi, const double *rr, const double *ri, double *m2r,
     double *m2i, double *r2r, double *r2i, double *wr, double *wi, int64_t n, int64_t ld,
     double inv) {
   int64_t i, j;
-  frechet_tile(listed, i, j);
+  frechet_element<TILES>(listed, i, j);
   if (i >= n || j >= n) return;
   double ar = 0.0, ai = 0.0;
-  for (int64_t q = ptr[i]; q < ptr[i + 1]; ++q) {
-    const int64_t o = int64_t(col[q]) * ld + j;
-    ar += val[q] * mr[o];
-    ai += val[q] * mi[o];
-  }
   const int64_t o = i * ld + j;
-  const double vr = inv * (tau * ai + rr[o]);
-  const double vi = inv * (-tau * ar + ri[o]);
-  m2r[o] = vr;
-  m2i[o] = vi;
-  wr[o] += vr;
-  wi[o] += vi;
-  frechet_right(ptr, col, val, rr, ri, i, j, ld, ar, ai);
-  r2r[o] = inv * tau * ai;
-  r2i[o] = -inv * tau * ar;
+  if constexpr (PARTS & kFrechetLeft) {
+    for (int64_t q = ptr[i]; q < ptr[i + 1]; ++q) {
+      const int64_t x = int64_t(col[q]) * ld + j;
+      ar += val[q] * mr[x];
+      ai += val[q] * mi[x];
+    }
+    const double vr = inv * (tau * ai + rr[o]);
+    const double vi = inv * (-tau * ar + ri[o]);
+    m2r[o] = vr;
+    m2i[o] = vi;
+    wr[o] += vr;
+    wi[o] += vi;
+  }
+  if constexpr (PARTS & kFrechetRight) {
+    frechet_right(ptr, col, val, rr, ri, i, j, ld, ar, ai);
+    r2r[o] = inv * tau * ai;
+    r2i[o] = -inv * tau * ar;
+  }
 }
 
 // out[e] = Im W[col_e][row_e] * val_e  (tr(W H_p) gathers W transposed)
@@ -786,16 +815,21 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
     auto [r_re, r_im] = dpl(L.fr);
     auto [r2_re, r2_im] = dpl(L.fr2);
     const int64_t total = int64_t(pe);
-    const dim3 eb(256), eg(unsigned((total + 255) / 256)), tb(1024);
+    const dim3 eb(256), eg(unsigned((total + 255) / 256));
     hipLaunchKernelGGL(widen_kernel<T>, eg, eb, 0, s, g_re, g_im, m_re, m_im, total);
     ADJ_OK(hipGetLastError());
     const double tau = dt;
-    const int32_t *tiles = series ? listed : nullptr;
+    const bool by_tiles = frechet_by_tiles(c->h, series ? int64_t(c->adj_tiles.size()) : 0);
+    const bool by_list = by_tiles && series;
+    const int32_t *tiles = by_list ? listed : nullptr;
     const unsigned edge = unsigned((n + 31) / 32);
-    const dim3 sg = series ? dim3(unsigned(c->adj_tiles.size())) : dim3(edge, edge);
-    if (series)   // (M holds all of G, zeros outside the listed tiles)
+    const dim3 tb(by_tiles ? 1024 : 256);
+    const dim3 sg = by_list    ? dim3(unsigned(c->adj_tiles.size()))
+                    : by_tiles ? dim3(edge, edge)
+                               : dim3(unsigned((n + 255) / 256), unsigned(n));
+    if (by_list)   // (M holds all of G, zeros outside the listed tiles)
       for (double *p : {r_re, m2_re, r2_re}) ADJ_OK(hipMemsetAsync(p, 0, 2 * pe * sizeof(double), s));
-    hipLaunchKernelGGL(frechet_begin_kernel, sg, tb, 0, s, c->h_ptr, c->h_col, c->h_val, tiles, tau,
+    hipLaunchKernelGGL(by_tiles ? frechet_begin_kernel<true> : frechet_begin_kernel<false>, sg, tb, 0, s, c->h_ptr, c->h_col, c->h_val, tiles, tau,
                        m_re, m_im, r_re, r_im, w_re, w_im, n, ld);
     ADJ_OK(hipGetLastError());
     // number of terms: theta^k / k! below 1e-18 with theta = tau |H|_1
@@ -807,10 +841,17 @@ static qme_status adjoint_impl(qme_ctx *c, const void *state0, int64_t n_steps, 
     }
     for (int k = 1; k <= kmax; ++k) {
       const double inv = 1.0 / double(k + 1);
-      hipLaunchKernelGGL(frechet_term_kernel, sg, tb, 0, s, c->h_ptr, c->h_col, c->h_val, tiles,
-                         tau, m_re, m_im, r_re, r_im, m2_re, m2_im, r2_re, r2_im, w_re, w_im, n,
-                         ld, inv);
-      ADJ_OK(hipGetLastError());
+      auto term = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, sg, tb, 0, s, c->h_ptr, c->h_col, c->h_val, tiles, tau, m_re, m_im,
+                           r_re, r_im, m2_re, m2_im, r2_re, r2_im, w_re, w_im, n, ld, inv);
+        return hipGetLastError();
+      };
+      if (by_tiles) {
+        ADJ_OK((term(frechet_term_kernel<true, kFrechetLeft | kFrechetRight>)));
+      } else {
+        ADJ_OK((term(frechet_term_kernel<false, kFrechetLeft>)));
+        ADJ_OK((term(frechet_term_kernel<false, kFrechetRight>)));
+      }
       std::swap(m_re, m2_re);
       std::swap(m_im, m2_im);
       std::swap(r_re, r2_re);
