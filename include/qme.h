@@ -591,8 +591,9 @@ qme_status qme_set_direct_loads(qme_ctx *ctx, int32_t mode);
  * 0 as a dense matrix in two matrix products, 1 by its Taylor series in two
  * passes over the rows of the state (H is sparse: a few multiply-adds per
  * element and term in place of N), -1 (default) by the series where it is the
- * faster form (a rule on N, H's couplings and |H dt|) and qme_set_split has
- * not asked for split products.  Tiles, splits and direct loads are knobs of
+ * faster form (a rule on N, H's couplings, |H dt| and whether the steps fold,
+ * qme_set_fold; a batch's do not) and qme_set_split has not asked for split
+ * products.  Tiles, splits and direct loads are knobs of
  * the dense products.  The forms agree to rounding.  Systems of up to 32 states
  * take the entries of dU or, by default where it is the faster form, the series
  * inside their single-workgroup path (qme_set_fused): 0 leaves only dU, 1 is

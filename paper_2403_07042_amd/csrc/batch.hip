@@ -463,7 +463,7 @@ static qme_status build_tables(qme_batch *b) {
     if (t.sparse.n_csr > 0 || t.sparse.koff_ptr) b->sparse = true;
     const int td = int((c->n + TD - 1) / TD);
     groups[i] = {0, 0};
-    if (uses_series(c)) {
+    if (uses_series(c, false)) {   // (a batch's steps do not fold)
       const int cls = series_slot_bytes(c->n) == 16 ? 0 : 1, rows = cls == 0 ? 4 : 2;
       groups[i][cls] = (c->n + rows - 1) / rows;
       b->series_n[cls] = std::max(b->series_n[cls], c->n);

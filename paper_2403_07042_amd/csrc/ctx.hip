@@ -298,9 +298,13 @@ template hipError_t step_once<double>(qme_ctx *, const void *, void *, void *, v
 // its blocks reads the N diagonal values of the rotated state once more).
 static constexpr int64_t kFuseTraceMaxN = 1024;
 
-bool uses_series(const qme_ctx *c) {
+bool uses_series(const qme_ctx *c, bool folds) {
   if (c->series_order == 0 || c->products == 0) return false;
-  return c->products == 1 || (c->series_faster && !c->split_asked);
+  return c->products == 1 || (c->series_faster[folds] && !c->split_asked);
+}
+
+bool uses_series(const qme_ctx *c) {
+  return uses_series(c, c->fold && c->jt.n_gather == 0 && c->jt.n_csr == 0);
 }
 
 bool fuse_trace_applies(const qme_ctx *c) {
@@ -700,9 +704,9 @@ static qme_status finish_context(qme_ctx *c, int32_t precision, void *hip_stream
       // several launches per step)
       if (n > kSmallN) {
         c->series_order = sp.order;
-        const bool folded = c->jt.n_gather == 0 && c->jt.n_csr == 0;
-        c->series_faster = sp.faster && series_step_us(sp, n, int(c->elem), folded, c->cus) <
-                                            dense_step_us(c->precision, n);
+        for (int folds = 0; folds < 2; ++folds)
+          c->series_faster[folds] = sp.faster && series_step_us(sp, n, int(c->elem), folds != 0, c->cus) <
+                                                     dense_step_us(c->precision, n);
         c->pure_series_faster = pure_series_us(sp, n, int(c->elem)) < pure_dense_us(n, int(c->elem));
       } else {
         c->small_order = sp.order;

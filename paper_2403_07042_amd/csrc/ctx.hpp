@@ -47,7 +47,8 @@ struct qme_ctx {
   // the propagator as a series (plan_series); series_order 0: none
   int series_order = 0;
   int small_order = 0, small_entries = 0;    // n <= kSmallN: SmallSeries
-  bool series_faster = false;                // than the dense products (the default's choice)
+  // than the dense products (the default's choice): [1] where steps fold, [0] where not
+  bool series_faster[2] = {false, false};
   bool pure_series_faster = false;           // the same for pure states
   double series_ratio[qme::kSeriesMaxOrder + 1] = {};
   bool series_phase = false;                 // the components' shifts differ
@@ -169,6 +170,7 @@ hipError_t step_once(qme_ctx *c, const void *in, void *out, void *y, void *z, hi
 // Whether the steps apply the propagator by its series (series_tile.hpp) or
 // multiply by the dense dU.
 bool uses_series(const qme_ctx *c);
+bool uses_series(const qme_ctx *c, bool folds);   // with the steps folded or not
 // Expected time of a step of a density matrix by the series or by dense
 // products, in us; folded: no decoherence pass (series.hip).
 double series_step_us(const SeriesPlan &p, int64_t n, int elem, bool folded, int cus);

@@ -168,3 +168,16 @@ def test_batch_takes_the_forms_at_config():
     assert sol.products == 1
     b.close()
     sol.close()
+
+
+def test_unfolded_steps_have_a_rule_of_their_own():
+    """Where the steps do not fold (fold off, batches), the series saves less: a
+    model on the line steps by it folded and by dense products unfolded."""
+    found = []
+    for n in (64, 100, 120, 200):
+        sol = P.Solver(ring(n, 4), "fp32")
+        folded = sol.products
+        sol.set_fold(False)
+        found.append((folded, sol.products))
+        sol.close()
+    assert found == [(0, 0), (1, 0), (1, 0), (1, 1)]
