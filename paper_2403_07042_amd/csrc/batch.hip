@@ -180,6 +180,9 @@ __global__ __launch_bounds__(kBatchThreads) void batch_phase_kernel(BatchPhase p
 // the latency of their loads and terms: 36.4 + 35.1 us with two slices
 // throughout and without xcd_run, with both the step went from 98.1 to 94.5 us.
 // Units of eight rows took 4% off there and cost 7 to 14% in smaller batches.
+// Batches of up to 64 or 128 states take workgroups of as many threads, without
+// waves that only wait: 64 of N = 64 20.3 -> 17.6 us per step (dense 18.6), 64 of N =
+// 128 31.7 -> 28.5 (36.5).
 template <int R, int S, int NT, int MODE>
 __global__ __launch_bounds__(NT, 4) void batch_series_kernel(BatchPhase p) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -195,6 +198,31 @@ __global__ __launch_bounds__(NT, 4) void batch_series_kernel(BatchPhase p) {
     }
   }
   series_rows<float, R, S, NT, MODE>(a, group, lds);
+}
+
+// A phase of a batch of both forms in one launch: the dense instances' tiles and
+// the series instances' row groups (N <= 256, whose workgroups have 256 threads
+// too) beside them.  A small batch's phase is one round of short workgroups, and a
+// launch of its own for each form cost more than the series saves: N = 24 and 128,
+// one each, 16.8 us per step with dense products throughout, 22.5 with two launches,
+// 14.8 so (three terms); 24 and 256 22.8, 23.5 and 16.1.
+template <int PHASE>
+__global__ __launch_bounds__(kBatchThreads, 4) void batch_both_kernel(BatchPhase dense, BatchPhase series,
+                                                                      unsigned tiles) {
+  __shared__ __align__(16) float smem[kGemmSmem];
+  if (blockIdx.x < tiles) {
+    const int64_t r = blockIdx.x;
+    const int lo = find_position(dense.off, dense.count, r);
+    batch_item<PHASE, false>(dense.inst[dense.order[lo]], int(r - dense.off[lo]), smem);
+  } else {
+    constexpr int kMode = PHASE == 0 ? kSeriesFirst : kSeriesLower;
+    const int64_t r = xcd_run(blockIdx.x - tiles, gridDim.x - tiles);
+    const int lo = find_position(series.off, series.count, r);
+    const int i = __builtin_amdgcn_readfirstlane(series.order[lo]);
+    const int group = __builtin_amdgcn_readfirstlane(int(r - series.off[lo]));
+    const SeriesArgs<float> &a = PHASE == 0 ? series.inst[i].first : series.inst[i].second;
+    series_rows<float, 4, 1, kBatchThreads, kMode>(a, group, reinterpret_cast<unsigned char *>(smem));
+  }
 }
 
 // After a run of fused steps that ended in slot pair 1, every instance's
@@ -582,6 +610,8 @@ static hipError_t enqueue_series_phase(qme_batch *b, int mode, hipStream_t s) {
     if (items == 0) continue;
     const BatchPhase p{b->inst, b->order, b->phase_off + (4 + cls) * (b->count + 1), b->count};
     const hipError_t e = cls == 1    ? enqueue_series<2, 8, 1024>(p, mode, items, s)
+                         : n <= 64   ? enqueue_series<4, 1, 64>(p, mode, items, s)
+                         : n <= 128  ? enqueue_series<4, 1, 128>(p, mode, items, s)
                          : n <= 256  ? enqueue_series<4, 1, 256>(p, mode, items, s)
                          : n <= 512  ? enqueue_series<4, 2, 256>(p, mode, items, s)
                          : n <= 1024 ? enqueue_series<4, 2, 512>(p, mode, items, s)
@@ -592,11 +622,35 @@ static hipError_t enqueue_series_phase(qme_batch *b, int mode, hipStream_t s) {
   return hipSuccess;
 }
 
+// Whether phase `ph` (0 or 1) takes both forms in one launch (batch_both_kernel):
+// while it is about one round of workgroups (four per CU); many more run better in
+// launches whose workgroups have the threads and LDS that each form needs (us per
+// step, one launch / two: 16 each of N = 24 and 256, 1088 workgroups, 39.1 / 44.3;
+// 64 each of 24 and 64, 1280, 27.1 / 29.5; of 24 and 128, 2304, 50.9 / 44.3).
+static bool both_in_one(const qme_batch *b, int ph) {
+  static_assert(2 * kBatchThreads * 4 <= kGemmSmem, "the series' rows fit the tiles' LDS");
+  return b->phase_items[ph] > 0 && b->phase_items[4] > 0 && b->phase_items[5] == 0 && b->series_n[0] <= 256 &&
+         b->phase_items[ph] + b->phase_items[4] <= 6 * int64_t(b->ctxs[0]->cus);
+}
+
 static hipError_t enqueue(qme_batch *b, int64_t n_steps, hipStream_t s) {
   if (b->persistent) return enqueue_persistent(b, n_steps, s);
   for (int64_t k = 0; k < n_steps; ++k) {
     const int parity = b->fuse ? int(k & 1) : 0;
     for (int ph = 0; ph < 4; ++ph) {
+      if (ph <= 1 && both_in_one(b, ph)) {
+        const BatchPhase dense{b->inst, b->order, b->phase_off + ph * (b->count + 1), b->count};
+        const BatchPhase series{b->inst, b->order, b->phase_off + 4 * (b->count + 1), b->count};
+        const unsigned tiles = unsigned(b->phase_items[ph]);
+        const dim3 grid(tiles + unsigned(b->phase_items[4]));
+        if (ph == 0)
+          hipLaunchKernelGGL(batch_both_kernel<0>, grid, dim3(kBatchThreads), 0, s, dense, series, tiles);
+        else
+          hipLaunchKernelGGL(batch_both_kernel<1>, grid, dim3(kBatchThreads), 0, s, dense, series, tiles);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        continue;
+      }
       if (ph <= 1) {
         const hipError_t e = enqueue_series_phase(b, ph == 0 ? kSeriesFirst : kSeriesLower, s);
         if (e != hipSuccess) return e;

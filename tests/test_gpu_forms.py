@@ -170,6 +170,58 @@ def test_batch_takes_the_forms_at_config():
     sol.close()
 
 
+def solo_unfolded(wl, form, tiles, steps, rho0):
+    sol = P.Solver(wl, "fp32")
+    sol.set_products(form)
+    sol.set_fold(False)
+    if form == 0:
+        sol.set_split(False)
+    sol.set_tiles(*tiles)
+    sol.set_rho(rho0)
+    sol.step(steps)
+    out = sol.get_rho()
+    sol.close()
+    return out
+
+
+@pytest.mark.parametrize("dense,series", [([40], [64]), ([24, 60], [63, 64]), ([200, 130], [65, 128]),
+                                          ([250], [129, 256, 40]), ([40], [257, 64]), ([], [64, 33]),
+                                          ([], [65, 128, 40]), ([], [129])])
+@pytest.mark.parametrize("tiles", [(32, 32), (64, 64)])
+def test_batches_of_small_systems_equal_solo(dense, series, tiles):
+    """The launches of a batch by its sizes and forms (both forms' workgroups in one
+    launch up to N = 256, workgroups of 64, 128 and 256 threads for the series
+    alone): every instance bitwise as alone, unfolded."""
+    sols, refs = [], []
+    for k, (n, form) in enumerate([(n, 0) for n in dense] + [(n, 1) for n in series]):
+        wl = dict(ring(n, 4), dt=0.02 + 0.05 * k)
+        psi = W.haar_psi(n, k)
+        rho0 = np.outer(psi, psi.conj())
+        if n > 32:
+            refs.append(solo_unfolded(wl, form, tiles, 7, rho0))
+        else:
+            refs.append(None)         # (alone it takes its single workgroup)
+        sol = P.Solver(wl, "fp32")
+        if n > 32:
+            sol.set_products(form)
+        sol.set_tiles(*tiles)
+        sol.set_rho(rho0)
+        sols.append(sol)
+    b = P.Batch(sols)
+    print(f"batch dense {dense} series {series} tiles {tiles}", flush=True)
+    b.step(3)
+    b.step(4)
+    torch.cuda.synchronize()
+    for sol, ref in zip(sols, refs):
+        rho, sink = sol.get_rho()
+        if ref is not None:
+            assert np.array_equal(rho, ref[0]) and sink == ref[1], sol.n
+        assert abs(np.trace(rho).real - 1.0) < 1e-6
+    b.close()
+    for sol in sols:
+        sol.close()
+
+
 def test_unfolded_steps_have_a_rule_of_their_own():
     """Where the steps do not fold (fold off, batches), the series saves less: a
     model on the line steps by it folded and by dense products unfolded."""
