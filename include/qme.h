@@ -446,7 +446,8 @@ typedef struct qme_batch qme_batch;
  * layouts from qme_state_layout, 256-byte aligned) into a batch.  Each step
  * of the batch is one launch per phase (first product, lower-triangle
  * product, trace/sink pass, decoherence pass; the first two once more for
- * instances that step by the series) covering the tiles of every
+ * instances that step by the series, where these do not fit beside the
+ * others) covering the tiles of every
  * instance, largest instances first; a run of n steps is captured once into
  * a hipGraph and replayed.  Each instance's two products run in the tile
  * edges of its context (qme_set_tiles; 32 or 64, else QME_E_UNSUPPORTED),
